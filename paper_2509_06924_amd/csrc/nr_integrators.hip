@@ -80,44 +80,73 @@ __global__ __launch_bounds__(256) void k_vi_sample(int64_t n_samples, int P, int
     bkg[i] = v;
 }
 
-// One thread per variational entry p: sums over samples in order.
+// Per variational entry p, sums over the samples:
 //   dELBO/dmu_p    = mean_i g_ip
 //   dELBO/domega_p = mean_i g_ip eps_ip s'(omega_p) + s'(omega_p)/s(omega_p)
 // (the last term is the gradient of the entropy sum_p ln s(omega_p)); zero for
-// entries outside the mask.  Thread P also forms the ELBO estimate
+// entries outside the mask.  Entry P stands for the ELBO estimate
 // mean_i logL_i + sum_p ln s(omega_p) (the Gaussian entropy up to its
 // constant).
-__global__ __launch_bounds__(256) void k_vi_reduce(int64_t n_samples, int P, int rows,
-                                                   const double* omega, const uint8_t* mask,
-                                                   const double* eps, const double* logL,
-                                                   const double* g_rows, const double* g_inst,
-                                                   double* grad_mu, double* grad_omega,
-                                                   double* elbo) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < P) {
-    if (!mask[p]) {
-      grad_mu[p] = 0.0;
-      grad_omega[p] = 0.0;
-      return;
+//
+// A block of 256 x 4 threads takes four neighbouring entries (one 32-byte
+// sector of a sample's row per load) and its threads every 256th sample; the
+// partial sums are added in a fixed order.  The kernel is bound by the latency
+// of its loads: one thread per entry walking the samples one by one took
+// 440 us at 1024 samples x 90 entries (four waves on the chip), this form 7 us.
+constexpr int kViEntries = 4, kViLanes = 256;
+__global__ __launch_bounds__(kViEntries* kViLanes) void k_vi_reduce(
+    int64_t n_samples, int P, int rows, const double* omega, const uint8_t* mask,
+    const double* eps, const double* logL, const double* g_rows, const double* g_inst,
+    double* grad_mu, double* grad_omega, double* elbo) {
+  constexpr int kWaves = kViEntries * kViLanes / 64;
+  __shared__ double part[kWaves][kViEntries][2];
+  const int e = threadIdx.x % kViEntries, l = threadIdx.x / kViEntries;
+  const int p = blockIdx.x * kViEntries + e;
+  double gm = 0.0, ge = 0.0;
+  if (p < P && mask[p]) {
+    const bool row = p < rows * 4;
+    const double* g = row ? g_rows + p : g_inst + (p - rows * 4);
+    const int64_t stride = row ? (int64_t)rows * 4 : 2;
+#pragma unroll 4
+    for (int64_t i = l; i < n_samples; i += kViLanes) {
+      const double v = g[i * stride];
+      gm += v;
+      ge = fma(v, eps[i * P + p], ge);
     }
-    double gm = 0.0, ge = 0.0;
-    for (int64_t i = 0; i < n_samples; ++i) {
-      const double g = (p < rows * 4) ? g_rows[i * rows * 4 + p] : g_inst[i * 2 + (p - rows * 4)];
-      gm += g;
-      ge = fma(g, eps[i * P + p], ge);
-    }
+  } else if (p == P) {
+#pragma unroll 4
+    for (int64_t i = l; i < n_samples; i += kViLanes) gm += logL[i];
+    for (int q = l; q < P; q += kViLanes)
+      if (mask[q]) ge += log(softplus(omega[q]));
+  }
+#pragma unroll
+  for (int off = 32; off >= kViEntries; off >>= 1) {
+    gm += __shfl_xor(gm, off, 64);
+    ge += __shfl_xor(ge, off, 64);
+  }
+  if (threadIdx.x % 64 < kViEntries) {
+    part[threadIdx.x / 64][e][0] = gm;
+    part[threadIdx.x / 64][e][1] = ge;
+  }
+  __syncthreads();
+  if (threadIdx.x >= kViEntries || p > P) return;
+  gm = 0.0;
+  ge = 0.0;
+  for (int v = 0; v < kWaves; ++v) {
+    gm += part[v][e][0];
+    ge += part[v][e][1];
+  }
+  if (p == P) {
+    *elbo = gm / (double)n_samples + ge;
+  } else if (!mask[p]) {
+    grad_mu[p] = 0.0;
+    grad_omega[p] = 0.0;
+  } else {
     const double inv = 1.0 / (double)n_samples;
     const double sp = sigmoid(omega[p]);
     const double s = softplus(omega[p]);
     grad_mu[p] = gm * inv;
     grad_omega[p] = ge * inv * sp + sp / s;
-  } else if (p == P) {
-    double ll = 0.0;
-    for (int64_t i = 0; i < n_samples; ++i) ll += logL[i];
-    double h = 0.0;
-    for (int q = 0; q < P; ++q)
-      if (mask[q]) h += log(softplus(omega[q]));
-    *elbo = ll / (double)n_samples + h;
   }
 }
 
@@ -169,8 +198,9 @@ hipError_t launch_vi_reduce(int64_t n_samples, int P, int rows, const double* om
                             const uint8_t* mask, const double* eps, const double* logL,
                             const double* g_rows, const double* g_inst, double* grad_mu,
                             double* grad_omega, double* elbo, hipStream_t st) {
-  hipLaunchKernelGGL(k_vi_reduce, grid_for((int64_t)P + 1), dim3(256), 0, st, n_samples, P, rows,
-                     omega, mask, eps, logL, g_rows, g_inst, grad_mu, grad_omega, elbo);
+  hipLaunchKernelGGL(k_vi_reduce, dim3((unsigned)(P / kViEntries + 1)),
+                     dim3(kViEntries * kViLanes), 0, st, n_samples, P, rows, omega, mask, eps, logL,
+                     g_rows, g_inst, grad_mu, grad_omega, elbo);
   return hipGetLastError();
 }
 
