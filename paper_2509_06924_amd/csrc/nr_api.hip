@@ -116,7 +116,7 @@ void append_math_tables(std::vector<double>& v) {
 // partial groups of several items of equal depth, lane by lane.
 struct Launch {
   int bucket = 0;
-  bool store = false;  // gradient: store variant (else recompute)
+  int form = kFormRecompute;  // gradient: the kernel form (resolution calls take their own)
   bool tail = false;
   bool split = false;  // split tail units (one item's partial group, lanes over node groups)
   int scan_ch = 0;     // deep lists: the largest levels-per-lane of its items at 64 lanes
@@ -171,7 +171,7 @@ struct nr_plan {
   int device = 0;
   int32_t n_datasets = 0, n_items = 0, precision = NR_F64;
   nr_plan_options opts;
-  bool bucket_store[kNumBuckets];
+  int bucket_form[kNumBuckets];  // GradForm of the plain gradient
   std::vector<int64_t> q_off, row_off, out_off;
   std::vector<int32_t> dataset_of_item;
   std::vector<double> dqq;
@@ -293,7 +293,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st,
 nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, bool events,
                        bool res) {
   {
-    hipError_t e = launch_item_consts(p->d_row_off, a.layers, const_cast<double*>(a.consts),
+    hipError_t e = launch_item_consts(p->precision, p->d_row_off, a.layers, const_cast<double*>(a.consts),
                                       const_cast<float*>(a.constsf), p->n_items, st);
     if (e != hipSuccess) return hip_fail(e, "constants launch");
   }
@@ -330,7 +330,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     a.tail_item = L.lane_item;
     a.tail_pt = L.lane_pt;
     a.tail_rec = L.lane_rec;
-    const int form = res ? kFormRecomputeRes : L.store ? kFormStore : kFormRecompute;
+    const int form = res ? kFormRecomputeRes : L.form;
     const int mode = L.tail ? kModeTail : L.split ? kModeSplit : kModeFull;
     const hipStream_t ls = (fork && L.side) ? p->side : st;
     if (!grad)
@@ -682,24 +682,28 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       (o.side_stream != 0 && o.side_stream != 1) ||
       !(o.node_groups == 0 || (o.node_groups >= 2 && o.node_groups <= kSmearNodes)))
     return NR_EINVAL;
-  bool bucket_store[kNumBuckets];
+  int bucket_form[kNumBuckets];
   for (int k = 0; k < kNumBuckets; ++k) {
     const int v = o.grad_variant[k];
     const bool can_store = kBucketLmax[k] <= store_max_layers(d->precision);
     if (v == NR_VARIANT_AUTO) {
-      bucket_store[k] = kBucketLmax[k] <= default_store_layers(d->precision);
+      bucket_form[k] = kBucketLmax[k] <= default_store_layers(d->precision) ? kFormStore
+                       : d->precision == NR_F64 && kBucketLmax[k] >= kSelectMinLayers &&
+                               kBucketLmax[k] <= kSelectMaxLayers
+                           ? kFormSelect
+                           : kFormRecompute;
     } else if (v == NR_VARIANT_STORE) {
       if (!can_store) return NR_EINVAL;
-      bucket_store[k] = true;
+      bucket_form[k] = kFormStore;
     } else if (v == NR_VARIANT_RECOMPUTE) {
-      bucket_store[k] = false;
+      bucket_form[k] = kFormRecompute;
     } else {
       return NR_EINVAL;
     }
   }
   nr_plan* p = new nr_plan();
   p->opts = o;
-  for (int k = 0; k < kNumBuckets; ++k) p->bucket_store[k] = bucket_store[k];
+  for (int k = 0; k < kNumBuckets; ++k) p->bucket_form[k] = bucket_form[k];
   if (hipGetDevice(&p->device) != hipSuccess) {
     delete p;
     return NR_EHIP;
@@ -973,7 +977,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
           }
       Launch L;
       L.bucket = bk;
-      L.store = p->bucket_store[bk];
+      L.form = p->bucket_form[bk] == kFormSelect ? kFormRecompute : p->bucket_form[bk];
       L.tail = true;
       L.n_wu = (int)b_item[bk].size();
       e = upload(&L.item, b_item[bk]);
@@ -1003,7 +1007,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       }
       Launch L;
       L.bucket = std::min(bk, kDeepBucket);
-      L.store = bk < kNumBuckets && p->bucket_store[bk];
+      L.form = bk < kNumBuckets ? p->bucket_form[bk] : kFormRecompute;
       L.scan_ch = bk >= kDeepBucket ? std::max(scan_ch[bk - kDeepBucket], 1) : 0;
       L.split = split;
       L.n_wu = (int)v.size();

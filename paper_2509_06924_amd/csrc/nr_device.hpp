@@ -265,6 +265,102 @@ __device__ __forceinline__ Root kz_root(double x, double y) {
 }
 
 // ---------------------------------------------------------------------------
+// The same functions with the argument given as a product c v whose constant
+// is already in units of the table step (c = C 64/pi or C 64/ln 2, formed per
+// row in twice the precision and rounded once).  The reduction is then
+// k = round(c v), r = c v - k in one FMA: no product, no two-term reduction,
+// and r carries one rounding instead of three.
+// ---------------------------------------------------------------------------
+constexpr double kPi64 = 0.04908738521234051935;     // pi/64
+constexpr double kLn264 = 0.01083042469624914546;    // ln(2)/64
+constexpr double k64OverPi = 20.371832715762602978;  // 64/pi
+constexpr double k64OverLn2 = 92.332482616893656768;  // 64/ln 2
+
+// sin and cos of c v pi/64: polynomials of r pi/64, |r| <= 1/2, to the same
+// orders as sincos_issue.
+__device__ __forceinline__ SinCosPart sincos_issue_scaled(const MathTables& T, double c,
+                                                          double v) {
+  constexpr double h = kPi64, h2 = h * h;
+  const double t = fma(c, v, kShift);
+  const double r = fma(c, v, -(t - kShift));
+  const int idx = low_word(t) & 127;
+  const lds_double* row = (const lds_double*)(&T.sc[idx][0]);
+  SinCosPart o;
+  o.sa = row[0];
+  o.ca = row[1];
+  const double r2 = r * r;
+  double ps = -h * h2 * h2 * h2 / 5040.0;
+  ps = fma(ps, r2, h * h2 * h2 / 120.0);
+  ps = fma(ps, r2, -h * h2 / 6.0);
+  ps = fma(ps, r2, h);
+  o.sr = r * ps;
+  double pc = -h2 * h2 * h2 / 720.0;
+  pc = fma(pc, r2, h2 * h2 / 24.0);
+  pc = fma(pc, r2, -0.5 * h2);
+  o.cr = fma(r2, pc, 1.0);
+  return o;
+}
+
+// Polynomial of e^(r ln2/64), |r| <= 1/2, to the order of exp_issue, and the
+// table read of n = round(c v) given as t = kShift + n.
+__device__ __forceinline__ ExpPart exp_part_scaled(const MathTables& T, double t, double r) {
+  constexpr double h = kLn264;
+  const int ni = low_word(t);
+  ExpPart o;
+  o.m = ni >> 6;
+  o.tj = ((const lds_double*)(&T.e2[0]))[ni & 63];
+  double p = h * h * h * h * h / 120.0;
+  p = fma(p, r, h * h * h * h / 24.0);
+  p = fma(p, r, h * h * h / 6.0);
+  p = fma(p, r, 0.5 * h * h);
+  p = fma(p, r, h);
+  o.p = fma(p, r, 1.0);
+  return o;
+}
+// e^(c v ln2/64), clamped like exp_issue (in units of ln2/64).
+__device__ __forceinline__ ExpPart exp_issue_scaled(const MathTables& T, double c, double v) {
+  const double y = fmin(fmax(c * v, -68880.0), 65556.0);
+  const double t = y + kShift;
+  return exp_part_scaled(T, t, y - (t - kShift));
+}
+// The same without the clamp, for |c v| < 2^31.
+__device__ __forceinline__ ExpPart exp_issue_bounded(const MathTables& T, double c, double v) {
+  const double t = fma(c, v, kShift);
+  return exp_part_scaled(T, t, fma(c, v, -(t - kShift)));
+}
+
+// e^x for |x| <= 2^-6 (Taylor to x^6, truncation 2^-54 relative), and sin x,
+// cos x for |x| <= 2^-8 (to x^5 and x^4, truncation 2^-68 and 2^-57).
+__device__ __forceinline__ double exp_small(double x) {
+  double p = fma(x, 1.0 / 720.0, 1.0 / 120.0);
+  p = fma(p, x, 1.0 / 24.0);
+  p = fma(p, x, 1.0 / 6.0);
+  p = fma(p, x, 0.5);
+  p = fma(p, x, 1.0);
+  return fma(p, x, 1.0);
+}
+__device__ __forceinline__ void sincos_small(double x, double* sn, double* cs) {
+  const double x2 = x * x;
+  *sn = fma(x * x2, fma(x2, 1.0 / 120.0, -1.0 / 6.0), x);
+  *cs = fma(x2, fma(x2, 1.0 / 24.0, -0.5), 1.0);
+}
+
+// kz and 1/|w| of w = x - i b for x > 0 and 0 <= b <= 2^-8 x: one reciprocal
+// square root and the binomial series of (1 - i b/x)^(1/2) and
+// (1 + (b/x)^2)^(-1/2), truncated below 2^-53.
+__device__ __forceinline__ Root kz_root_above(double x, double b) {
+  const double r = rsq(x);
+  const double s = x * r, r2 = r * r;
+  const double be = b * r2;
+  const double v = 0.125 * be * be;
+  Root out;
+  out.kz.re = fma(s * v, fma(v, -2.5, 1.0), s);
+  out.kz.im = -(b * r) * fma(v, fma(v, 1.75, -0.5), 0.5);
+  out.inv_abs2 = r2 * fma(v, fma(v, 24.0, -4.0), 1.0);
+  return out;
+}
+
+// ---------------------------------------------------------------------------
 // FP32 variant.  The hardware transcendentals of gfx950 are used directly:
 // v_rcp_f32, v_rsq_f32 (about 1 ulp), v_exp_f32 (2^x), v_sin_f32 and
 // v_cos_f32 (of 2 pi x, for |x| <= 256; the argument is reduced to

@@ -17,10 +17,13 @@ constexpr int kWuPoints = 64;  // data points per work unit (one per lane)
 // stacks recompute them.
 constexpr int kStoreMaxLayers = 10;
 constexpr int kStoreMaxLayersF32 = 10;
-// Per-row layer records in the workspace: 6 doubles, then (in a second
-// array) 8 floats.
+// Per-row layer records in the workspace: 6 doubles, then in a second array
+// 8 floats (FP32 plans) or 4 doubles (FP64 plans).
 constexpr int kRecDoubles = 6;
 constexpr int kRecFloats = 8;
+constexpr int kExtDoubles = 4;
+static_assert(kRecFloats * sizeof(float) == kExtDoubles * sizeof(double),
+              "the second array's rows have one size in both precisions");
 
 constexpr uint32_t kItemNonfinite = NR_ITEM_NONFINITE;
 constexpr uint32_t kItemBadQ = NR_ITEM_BAD_Q;
@@ -89,7 +92,8 @@ struct KernelArgs {
   const double* seed;
   double* rec;     // workspace records
   const double* consts;  // workspace: per-item layer records (6 doubles per row)
-  const float* constsf;  // workspace: their float copies (8 floats per row)
+  const float* constsf;  // workspace: second array (FP32: float copies, 8 per row; FP64: the
+                         // scaled exponent factors, 4 doubles per row)
   // plan-owned constants (device): quadrature node offsets in units of
   // sigma_Q and normalised weights (kSmearNodes each), then the tables
   // (sin, cos)(k pi/64) for k = 0..127 interleaved and 2^(j/64), j = 0..63
@@ -112,16 +116,17 @@ struct ReduceArgs {
   int32_t max_rows;  // the largest rows of any item (record length)
 };
 
-hipError_t launch_item_consts(const int64_t* row_off, const double* layers, double* rec,
-                              float* recf, int n_items, hipStream_t st);
+hipError_t launch_item_consts(int precision, const int64_t* row_off, const double* layers,
+                              double* rec, float* recf, int n_items, hipStream_t st);
 // precision: NR_F64 or NR_F32
 hipError_t launch_forward(int precision, int op, bool split, const KernelArgs& a, int n_wu,
                           hipStream_t st);
 // store: the store variant (only for buckets within store_max_layers)
 // Forms of the gradient kernel: the recompute form, the store form (buckets up
 // to the precision's store limit), and the recompute form that also
-// accumulates the derivative with respect to the relative resolution.
-enum GradForm { kFormRecompute = 0, kFormStore = 1, kFormRecomputeRes = 2 };
+// accumulates the derivative with respect to the relative resolution; and
+// (FP64) the kernels that choose between two node forms (nr_select.hpp).
+enum GradForm { kFormRecompute = 0, kFormStore = 1, kFormRecomputeRes = 2, kFormSelect = 3 };
 // mode: kModeFull (64 points of one item), kModeTail (packed partial
 // groups of several items), kModeSplit (one item's partial group, lanes over
 // node groups x points)
@@ -155,6 +160,11 @@ inline int store_max_layers(int precision) {
 // waves per SIMD) up to 4 layers (0.71 vs 0.60 of peak) and loses from 6 on
 // (10 layers: 0.56 vs 0.60); FP32 store wins up to 8 layers.
 inline int default_store_layers(int precision) { return precision == NR_F32 ? 8 : 4; }
+// Buckets whose default is the select form (FP64; packed tail units take the
+// recompute form): 4-7 % faster than the recompute form at 6-16 layers, 1-2 %
+// at 18 and 20, within 1 % at 24-32, 4 % slower at 40 (nr_select.hpp).  Up to 4
+// layers the store form stays.
+constexpr int kSelectMinLayers = 6, kSelectMaxLayers = 20;
 hipError_t launch_reduce(int op, const ReduceArgs& a, hipStream_t st);
 // Allows the gradient reduction its dynamic LDS for records of max_rows media.
 hipError_t prepare_reduce(int max_rows);

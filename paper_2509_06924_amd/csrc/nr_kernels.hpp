@@ -1086,82 +1086,15 @@ __device__ __forceinline__ double node_grad_recompute(const MathTables& T, const
   return (double)cabs2(r);
 }
 
-// ---------------------------------------------------------------------------
-// logL + gradient partials per WU (nr_loglik_grad).
-// Record layout (NR = N + 2 media):
-//   [0] logL, [1] d/dscale, [2] d/dbkg,
-//   [3 + m]        sum Re wbar_m     (wbar_m = cotangent of w_m = kz_m^2)
-//   [3 + NR + m]   sum Im wbar_m
-//   [3 + 2NR + m]  sum dl/dd_m
-//   [3 + 3NR + m]  sum Re(conj(ubar) kz_{m-1} kz_m)   (sigma_m factor applied later)
-//   [3 + 4NR]      d/d(dQ/Q) (relative resolution)
-// ---------------------------------------------------------------------------
-template <class P, int LMAX, bool STORE, bool TAIL, bool RES, bool SPLIT = false>
-__global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void k_loglik_grad(
-    KernelArgs a) {
-  static_assert(!(STORE && RES), "the resolution derivative has the recompute form only");
-  static_assert(!(TAIL && SPLIT), "a unit is packed or split, not both");
-  using Re = typename P::real;
-  __shared__ Shared s;
-  using Tape = typename std::conditional<STORE, GradTape<Re, LMAX>, char>::type;
-  __shared__ Tape tape;
-  constexpr int KS = STORE ? 1 : P::ef_levels(LMAX);
-  constexpr int KE = STORE ? 0 : P::e_levels(LMAX);
-  using Ef = typename std::conditional<STORE, char, EfCache<Re, KS, KE>>::type;
-  __shared__ Ef efc;
-  const int lane = threadIdx.x;
-  const int w = blockIdx.x;
-  SplitInfo sp{0, 1, 64};
-  const WuInfo u = TAIL ? tail_setup(a, w, lane)
-                        : SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
-  stage_shared(s, lane, a.rule);
+// The end of a gradient unit: instrument, likelihood, seeds, and the unit's
+// record (stage: 4 + 4 (LMAX + 2) doubles of LDS that the sweeps no longer
+// read).
+template <int LMAX, bool TAIL, bool SPLIT, bool RES>
+__device__ __forceinline__ void write_grad_record(const KernelArgs& a, const WuInfo& u,
+                                                  const SplitInfo& sp, int w, int lane,
+                                                  Accum<LMAX>& acc, double Rsm, double Hq,
+                                                  bool badq, bool edge, double* stage) {
   const int N = u.N;
-  const int K = u.smeared ? kSmearNodes : 1;
-
-  Accum<LMAX> acc;
-#pragma unroll
-  for (int m = 0; m < LMAX + 2; ++m) {
-    acc.Hw[m] = mk(0.0, 0.0);
-    acc.Hd[m] = 0.0;
-    acc.Hs[m] = 0.0;
-  }
-
-  double Rsm = 0.0;
-  double Hq = 0.0;  // sum_k w_k dR(q_k)/dq_k dq_k/d(dQ/Q)
-  bool badq = !(u.Q > 0.0);
-  bool edge = false;
-  // dq_k/d(dQ/Q) = Q t_k / (2 sqrt(2 ln 2)) for a relative width
-  const double dq_dres = (u.smeared && !u.pointwise) ? u.Q / kFwhmPerSigma : 0.0;
-  // a split unit's lane takes every G-th node from its group's first
-  const int k0 = SPLIT ? (u.active ? sp.g : K) : 0;
-  const int kstep = SPLIT ? sp.G : 1;
-  for (int k = k0; k < K; k += kstep) {
-    const double tk = ld(s.t[k]);
-    const double q = (K == 1) ? u.Q : smear_at(u.Q, u.sig, tk);
-    badq |= !(q > 0.0);
-    const double wk = (K == 1) ? 1.0 : ld(s.w[k]);
-    const Layers<P> L = item_layers<P>(a, u.roff, N, k);
-    double R;
-    if constexpr (STORE)
-      R = node_grad_store<P, LMAX>(s.tab, L, tape, acc, lane, q, wk, edge);
-    else
-      R = node_grad_recompute<P, LMAX, KS, KE, P::checkpoint(LMAX), RES,
-                              P::pipelined(LMAX, TAIL || SPLIT || RES)>(
-          s.tab, L, efc, acc, lane, q, wk, edge, Hq, RES ? dq_dres * tk : 0.0);
-    Rsm += wk * R;
-  }
-  // the item was evaluated at depth LMAX: the copies of the backing below it
-  // (media N + 2 .. LMAX + 1) are the backing's parameters
-  {
-    cd back = mk(0.0, 0.0);
-#pragma unroll
-    for (int m = 1; m < LMAX + 2; ++m)
-      if (m >= N + 1) back += acc.Hw[m];
-#pragma unroll
-    for (int m = 1; m < LMAX + 2; ++m)
-      if (m == N + 1) acc.Hw[m] = back;
-  }
-
   if constexpr (SPLIT) {
     // the point's smeared R and its q test over its node groups' lanes
     double tot = 0.0;
@@ -1258,10 +1191,6 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
   // ---- wave reduction; the sums go through LDS into one coalesced store ----
   // (staged in the unit's tape or cache, which the sweeps no longer read; a
   // block is one wave, so its LDS accesses stay in program order)
-  using Sweep = typename std::conditional<STORE, Tape, Ef>::type;
-  static_assert(sizeof(Sweep) >= sizeof(double) * (4 + 4 * (LMAX + 2)),
-                "the record staging must fit in the sweep's LDS");
-  double* stage = STORE ? reinterpret_cast<double*>(&tape) : reinterpret_cast<double*>(&efc);
   ll = wave_sum(ll);
   gsc = wave_sum(gsc);
   gbk = wave_sum(gbk);
@@ -1294,6 +1223,90 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
   __syncthreads();
   double* rec = a.rec + a.wu_rec[w];
   for (int f = lane; f < nf; f += 64) rec[f] = stage[f];
+}
+
+// ---------------------------------------------------------------------------
+// logL + gradient partials per WU (nr_loglik_grad).
+// Record layout (NR = N + 2 media):
+//   [0] logL, [1] d/dscale, [2] d/dbkg,
+//   [3 + m]        sum Re wbar_m     (wbar_m = cotangent of w_m = kz_m^2)
+//   [3 + NR + m]   sum Im wbar_m
+//   [3 + 2NR + m]  sum dl/dd_m
+//   [3 + 3NR + m]  sum Re(conj(ubar) kz_{m-1} kz_m)   (sigma_m factor applied later)
+//   [3 + 4NR]      d/d(dQ/Q) (relative resolution)
+// ---------------------------------------------------------------------------
+template <class P, int LMAX, bool STORE, bool TAIL, bool RES, bool SPLIT = false>
+__global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void k_loglik_grad(
+    KernelArgs a) {
+  static_assert(!(STORE && RES), "the resolution derivative has the recompute form only");
+  static_assert(!(TAIL && SPLIT), "a unit is packed or split, not both");
+  using Re = typename P::real;
+  __shared__ Shared s;
+  using Tape = typename std::conditional<STORE, GradTape<Re, LMAX>, char>::type;
+  __shared__ Tape tape;
+  constexpr int KS = STORE ? 1 : P::ef_levels(LMAX);
+  constexpr int KE = STORE ? 0 : P::e_levels(LMAX);
+  using Ef = typename std::conditional<STORE, char, EfCache<Re, KS, KE>>::type;
+  __shared__ Ef efc;
+  const int lane = threadIdx.x;
+  const int w = blockIdx.x;
+  SplitInfo sp{0, 1, 64};
+  const WuInfo u = TAIL ? tail_setup(a, w, lane)
+                        : SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
+  stage_shared(s, lane, a.rule);
+  const int N = u.N;
+  const int K = u.smeared ? kSmearNodes : 1;
+
+  Accum<LMAX> acc;
+#pragma unroll
+  for (int m = 0; m < LMAX + 2; ++m) {
+    acc.Hw[m] = mk(0.0, 0.0);
+    acc.Hd[m] = 0.0;
+    acc.Hs[m] = 0.0;
+  }
+
+  double Rsm = 0.0;
+  double Hq = 0.0;  // sum_k w_k dR(q_k)/dq_k dq_k/d(dQ/Q)
+  bool badq = !(u.Q > 0.0);
+  bool edge = false;
+  // dq_k/d(dQ/Q) = Q t_k / (2 sqrt(2 ln 2)) for a relative width
+  const double dq_dres = (u.smeared && !u.pointwise) ? u.Q / kFwhmPerSigma : 0.0;
+  // a split unit's lane takes every G-th node from its group's first
+  const int k0 = SPLIT ? (u.active ? sp.g : K) : 0;
+  const int kstep = SPLIT ? sp.G : 1;
+  for (int k = k0; k < K; k += kstep) {
+    const double tk = ld(s.t[k]);
+    const double q = (K == 1) ? u.Q : smear_at(u.Q, u.sig, tk);
+    badq |= !(q > 0.0);
+    const double wk = (K == 1) ? 1.0 : ld(s.w[k]);
+    const Layers<P> L = item_layers<P>(a, u.roff, N, k);
+    double R;
+    if constexpr (STORE)
+      R = node_grad_store<P, LMAX>(s.tab, L, tape, acc, lane, q, wk, edge);
+    else
+      R = node_grad_recompute<P, LMAX, KS, KE, P::checkpoint(LMAX), RES,
+                              P::pipelined(LMAX, TAIL || SPLIT || RES)>(
+          s.tab, L, efc, acc, lane, q, wk, edge, Hq, RES ? dq_dres * tk : 0.0);
+    Rsm += wk * R;
+  }
+  // the item was evaluated at depth LMAX: the copies of the backing below it
+  // (media N + 2 .. LMAX + 1) are the backing's parameters
+  {
+    cd back = mk(0.0, 0.0);
+#pragma unroll
+    for (int m = 1; m < LMAX + 2; ++m)
+      if (m >= N + 1) back += acc.Hw[m];
+#pragma unroll
+    for (int m = 1; m < LMAX + 2; ++m)
+      if (m == N + 1) acc.Hw[m] = back;
+  }
+
+  using Sweep = typename std::conditional<STORE, Tape, Ef>::type;
+  static_assert(sizeof(Sweep) >= sizeof(double) * (4 + 4 * (LMAX + 2)),
+                "the record staging must fit in the sweep's LDS");
+  write_grad_record<LMAX, TAIL, SPLIT, RES>(
+      a, u, sp, w, lane, acc, Rsm, Hq, badq, edge,
+      STORE ? reinterpret_cast<double*>(&tape) : reinterpret_cast<double*>(&efc));
 }
 
 // ---------------------------------------------------------------------------

@@ -4,13 +4,56 @@
 #include <algorithm>
 
 #include "nr_kernels.hpp"
+#include "nr_select.hpp"
 
 namespace nr {
 
 NR_DEFINE_GRAD_LAUNCHER(launch_grad_shallow, NR_BUCKETS_SHALLOW)
 
+static hipError_t launch_select_shallow(int bucket, int mode, const KernelArgs& a, int n_wu,
+                                        hipStream_t st) {
+  if (n_wu <= 0) return hipSuccess;
+  if (mode == kModeTail) return hipErrorInvalidValue;
+  switch (kBucketLmax[bucket]) {
+#define NR_SELECT_CASE(LM)               \
+  case LM:                               \
+    if constexpr (LM >= kSelectMinLayers) { \
+      NR_SELECT_LAUNCH(LM)               \
+      return hipGetLastError();          \
+    }                                    \
+    break;
+    NR_BUCKETS_SHALLOW(NR_SELECT_CASE)
+#undef NR_SELECT_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+// c (hi + lo), rounded once; c = ch + cl.
+__device__ __forceinline__ double scaled_const(double ch, double cl, double hi, double lo) {
+  const double p = ch * hi;
+  return p + fma(ch, lo, fma(cl, hi, fma(ch, hi, -p)));
+}
+
 // One block of 64 per item, lanes over the media: the item's layer records
-// (doubles and their float copies for the FP32 variant).
+// (doubles), and the second array of the precision: EXT (FP64 plans) the
+// scaled exponent factors and the item's range of kz0^2 for the above-edge
+// node form (see LevelRecords), else (FP32) the float copies.
+//
+// The range [lo, hi] of kz0^2 in which every medium propagates and absorbs
+// little enough for the above-edge form, from bounds that hold for any stack:
+//   x_m = kz0^2 - A_m >= 256 B_m          series of kz_root_above
+//   |D_m Im kz_m| <= |D_m| B_m / (2 sqrt(x_m)) <= 2^-6     exp_small
+//   x_m >= (max A - min A) / 15, so that x_m / x_n <= 16 and
+//   |C_m Im(kz_m kz_m+1)| <= 2.1 |C_m| (B_m + B_m+1) <= 2^-8   sincos_small
+//   |C_m Re(kz_m kz_m+1)| <= 1.01 |C_m| (kz0^2 - min A) <= 1e7  exp_issue_bounded
+// A NaN or an infinity in the rows fails a comparison and empties the range.
+template <bool EXT>
 __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, const double* layers,
                                                     double* rec, float* recf, int n_items) {
   const int b = blockIdx.x;
@@ -18,31 +61,73 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
   const int64_t r0 = row_off[b];
   const int NR = (int)(row_off[b + 1] - r0);
   const double* rows = layers + 4 * r0;
-  for (int m = threadIdx.x; m < NR; m += 64) {
   const double rho0 = rows[1];
   auto Af = [&](int j) { return (j == 0) ? 0.0 : kFourPi * (rows[4 * j + 1] - rho0); };
   auto Bf = [&](int j) { return (j == 0) ? 0.0 : kFourPi * fabs(rows[4 * j + 2]); };
-  double v[kRecDoubles];
-  const double A = Af(m), B = Bf(m);
-  v[0] = A;
-  v[1] = B;
-  if (m + 1 < NR) {
-    const double sg = rows[4 * (m + 1) + 3];
-    v[2] = Af(m + 1) - A;
-    v[3] = Bf(m + 1) - B;
-    v[4] = -2.0 * (sg * sg);
-  } else {
-    v[2] = 0.0;
-    v[3] = 0.0;
-    v[4] = 0.0;
+  double amax = 0.0, amin = 0.0;
+  if constexpr (EXT) {
+    for (int m = threadIdx.x; m < NR; m += 64) {
+      amax = fmax(amax, Af(m));
+      amin = fmin(amin, Af(m));
+    }
+    amax = wave_max(amax);
+    amin = -wave_max(-amin);
   }
-  // the fronting and backing have no thickness (their rows' d is ignored)
-  v[5] = (m == 0 || m + 1 == NR) ? 0.0 : 2.0 * rows[4 * m];
-  double* out = rec + (r0 + m) * kRecDoubles;
-  for (int f = 0; f < kRecDoubles; ++f) out[f] = v[f];
-  float* outf = recf + (r0 + m) * kRecFloats;
-  for (int f = 0; f < 5; ++f) outf[f] = (float)v[f + 1];
-  for (int f = 5; f < kRecFloats; ++f) outf[f] = 0.0f;
+  double lo = 1e-30, hi = 1e300;
+  for (int m = threadIdx.x; m < NR; m += 64) {
+    double v[kRecDoubles];
+    const double A = Af(m), B = Bf(m);
+    v[0] = A;
+    v[1] = B;
+    double sg2 = 0.0, sg2_lo = 0.0;
+    if (m + 1 < NR) {
+      const double sg = rows[4 * (m + 1) + 3];
+      sg2 = sg * sg;
+      sg2_lo = fma(sg, sg, -sg2);
+      v[2] = Af(m + 1) - A;
+      v[3] = Bf(m + 1) - B;
+      v[4] = -2.0 * sg2;
+    } else {
+      v[2] = 0.0;
+      v[3] = 0.0;
+      v[4] = 0.0;
+    }
+    // the fronting and backing have no thickness (their rows' d is ignored)
+    v[5] = (m == 0 || m + 1 == NR) ? 0.0 : 2.0 * rows[4 * m];
+    double* out = rec + (r0 + m) * kRecDoubles;
+    for (int f = 0; f < kRecDoubles; ++f) out[f] = v[f];
+    if constexpr (EXT) {
+      // 64/pi and 64/ln 2 as sums of two doubles
+      constexpr double kPiLo = -1.259435307211679e-15, kLn2Lo = 1.3027375194195861e-15;
+      double* ext = reinterpret_cast<double*>(recf) + (r0 + m) * kExtDoubles;
+      if (m > 0) {
+        ext[0] = scaled_const(v[5], 0.0, k64OverPi, kPiLo);
+        ext[1] = scaled_const(v[5], 0.0, k64OverLn2, kLn2Lo);
+      }
+      ext[2] = scaled_const(v[4], -2.0 * sg2_lo, k64OverPi, kPiLo);
+      ext[3] = scaled_const(v[4], -2.0 * sg2_lo, k64OverLn2, kLn2Lo);
+      const double db = 32.0 * v[5] * B;
+      const double need = fmax(fmax(256.0 * B, db * db), (amax - amin) * (1.0 / 15.0));
+      const double bn = (m + 1 < NR) ? Bf(m + 1) : 0.0;
+      // (sums and products: a NaN term makes the comparison false)
+      const bool ok = A + 256.0 * B + db * db + v[2] + v[3] < 1e300 &&
+                      -2.1 * v[4] * (B + bn) <= 0x1p-8 && fabs(v[5]) < 1e12;
+      lo = fmax(lo, ok ? A + need : __builtin_inf());
+      hi = fmin(hi, amin - 9.9e6 / fmin(v[4], -1e-200));
+    } else {
+      float* outf = recf + (r0 + m) * kRecFloats;
+      for (int f = 0; f < 5; ++f) outf[f] = (float)v[f + 1];
+      for (int f = 5; f < kRecFloats; ++f) outf[f] = 0.0f;
+    }
+  }
+  if constexpr (EXT) {
+    lo = wave_max(lo);
+    hi = -wave_max(-hi);
+    if (threadIdx.x == 0) {
+      double* ext = reinterpret_cast<double*>(recf) + r0 * kExtDoubles;
+      ext[0] = lo;
+      ext[1] = hi;
+    }
   }
 }
 
@@ -171,11 +256,15 @@ __global__ __launch_bounds__(1024) void k_reduce_grad(ReduceArgs a) {
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_item_consts(const int64_t* row_off, const double* layers, double* rec,
-                              float* recf, int n_items, hipStream_t st) {
+hipError_t launch_item_consts(int precision, const int64_t* row_off, const double* layers,
+                              double* rec, float* recf, int n_items, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_item_consts, dim3(n_items), dim3(64), 0, st, row_off, layers, rec, recf,
-                     n_items);
+  if (precision == NR_F32)
+    hipLaunchKernelGGL(k_item_consts<false>, dim3(n_items), dim3(64), 0, st, row_off, layers, rec,
+                       recf, n_items);
+  else
+    hipLaunchKernelGGL(k_item_consts<true>, dim3(n_items), dim3(64), 0, st, row_off, layers, rec,
+                       recf, n_items);
   return hipGetLastError();
 }
 
@@ -200,6 +289,9 @@ hipError_t launch_grad(int precision, int bucket, int form, int mode, const Kern
         return hipErrorInvalidValue;
     }
   }
+  if (form == kFormSelect)
+    return precision == NR_F64 ? launch_select_shallow(bucket, mode, a, n_wu, st)
+                               : hipErrorInvalidValue;
   return precision == NR_F32 ? launch_grad_f32(bucket, form, mode, a, n_wu, st)
                              : launch_grad_shallow<F64>(bucket, form, mode, a, n_wu, st);
 }
