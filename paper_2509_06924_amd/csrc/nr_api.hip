@@ -334,7 +334,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     const int mode = L.tail ? kModeTail : L.split ? kModeSplit : kModeFull;
     const hipStream_t ls = (fork && L.side) ? p->side : st;
     if (!grad)
-      launch_err = launch_forward(p->precision, op, L.split, a, L.n_wu, ls);
+      launch_err = launch_forward(p->precision, op, a, L.n_wu, ls);
     else if (L.bucket == kDeepBucket)
       launch_err = launch_grad_scan(res, L.scan_ch, a, L.n_wu, ls);
     else
@@ -736,15 +736,14 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     int32_t item, p0, count;
     int64_t rec0;  // record of its first point
   };
-  // one list per bucket, then the deep lists: forward one (kDeepBucket),
-  // gradient three (kDeepBucket + c), by the levels per lane an item needs at
-  // 64 lanes (c = 0: up to 8, 1: up to 16, 2: more), which set the waves per
+  // gradient: one list per bucket, then three deep lists (kDeepBucket + c), by
+  // the levels per lane an item needs at 64 lanes (c = 0: up to 8, 1: up to 16, 2: more), which set the waves per
   // data point of the scan kernel (1, 2, 4), so that shallower deep items do
   // not run with the idle lanes of the deepest one
   constexpr int kDeepClasses = 3;
-  std::vector<std::vector<Wu>> fwd_units(kNumBuckets + 1);
+  std::vector<Wu> fwd_units;
   std::vector<std::vector<Wu>> grad_units(kNumBuckets + kDeepClasses);
-  std::vector<std::vector<Wu>> split_units(kNumBuckets), fwd_split_units(kNumBuckets);
+  std::vector<std::vector<Wu>> split_units(kNumBuckets);
   int scan_ch[kDeepClasses] = {0, 0, 0};
   std::map<std::pair<int, int>, std::vector<Tail>> tails;  // (depth, nodes)
   std::vector<int64_t> ll_first(nI), ll_offs, gr_first(nI), gr_offs;
@@ -770,11 +769,19 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) !=
         hipSuccess)
       cus = 0;
-    const int64_t round = 2 * 4 * (int64_t)cus;
-    if (units > 0 && units < round)
-      small_G = (int)std::min<int64_t>(kSmearNodes, round / units);
-    if (units_fwd > 0 && units_fwd < round)
-      small_G_fwd = (int)std::min<int64_t>(kSmearNodes, round / units_fwd);
+    const int64_t simds = 4 * (int64_t)cus;
+    if (units > 0 && units < 2 * simds)
+      small_G = (int)std::min<int64_t>(kSmearNodes, 2 * simds / units);
+    // Value units, by how many each SIMD would get unsplit.  Measured on MI355X
+    // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
+    // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
+    // 113 / 92 / 98 / 102; 2688: 147 / 130 / 137 / 139; 3584: 152 / 160 / 174 /
+    // 178.  G = 4 and 17 leave lanes or nodes over and are never the best.
+    if (units_fwd > 0)
+      small_G_fwd = 5 * units_fwd < 2 * simds   ? 9
+                    : 2 * units_fwd < 3 * simds ? 6
+                    : units_fwd < 3 * simds     ? 2
+                                                : 1;
   }
   // a tiling given by the caller: every point group split over node_groups
   if (p->opts.node_groups >= 2) small_G = p->opts.node_groups;
@@ -787,28 +794,19 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     const int64_t rsz = 4 + 4 * (N + 2);
     p->out_off[b + 1] = p->out_off[b] + nq;
     ll_first[b] = (int64_t)ll_offs.size();
-    if (K > 1 && small_G_fwd >= 2) {
-      // value units split like the gradient's (lane = g npts + p)
-      const int npts = kWuPoints / small_G_fwd;
-      int32_t cnt = 0;
+    {
+      // value units: groups of npts points, the last one of what is left; a
+      // smeared group of np points runs G = 64 / np node groups side by side
+      const int npts = K > 1 ? kWuPoints / small_G_fwd : kWuPoints;
       for (int64_t p0 = 0; p0 < nq; p0 += npts) {
         const int np = (int)std::min<int64_t>(npts, nq - p0);
-        Wu u{b, (int32_t)p0, rec_ll, (double)np * K * (N + 1)};
-        u.split = np | (small_G_fwd << 16);
-        fwd_split_units[std::min(bk, kNumBuckets - 1)].push_back(u);
-        ll_offs.push_back(rec_ll++);
-        ++cnt;
-      }
-      ll_count[b] = cnt;
-    } else {
-      const int nwu = (int)((nq + kWuPoints - 1) / kWuPoints);
-      ll_count[b] = nwu;
-      for (int k = 0; k < nwu; ++k) {
-        const int p0 = k * kWuPoints;
-        const double pts = (double)std::min<int64_t>(kWuPoints, nq - p0);
-        fwd_units[bk].push_back({b, p0, rec_ll, pts * K * (N + 1)});
+        const int G = std::min(kWuPoints / np, K);
+        Wu u{b, (int32_t)p0, rec_ll, (double)((K + G - 1) / G) * (N + 1)};
+        u.split = np | (G << 16);
+        fwd_units.push_back(u);
         ll_offs.push_back(rec_ll++);
       }
+      ll_count[b] = (int32_t)(ll_offs.size() - (size_t)ll_first[b]);
     }
     p->max_rows = std::max(p->max_rows, N + 2);
     if (bk == kDeepBucket) {
@@ -1019,8 +1017,11 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       out_list.push_back(L);
     }
   };
-  make_full(fwd_units, p->launches_fwd, false);
-  make_full(fwd_split_units, p->launches_fwd, true);
+  {
+    // the value kernels take any depth: one launch
+    std::vector<std::vector<Wu>> all{std::move(fwd_units)};
+    make_full(all, p->launches_fwd, true);
+  }
   make_full(grad_units, p->launches_grad, false);
   const size_t n_main = p->launches_grad.size();
   make_full(split_units, p->launches_grad, true);

@@ -271,6 +271,15 @@ __device__ __forceinline__ Root kz_root(double x, double y) {
 // k = round(c v), r = c v - k in one FMA: no product, no two-term reduction,
 // and r carries one rounding instead of three.
 // ---------------------------------------------------------------------------
+// a b + c for a constant c: the constant stays in scalar registers.  (Left to
+// itself the compiler takes the two-operand FMA and copies c into its
+// destination first: 16 register moves per level of the value kernel, 3 % of
+// its time.)
+__device__ __forceinline__ double fma_k(double a, double b, double c) {
+  double o;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(o) : "v"(a), "v"(b), "s"(c));
+  return o;
+}
 constexpr double kPi64 = 0.04908738521234051935;     // pi/64
 constexpr double kLn264 = 0.01083042469624914546;    // ln(2)/64
 constexpr double k64OverPi = 20.371832715762602978;  // 64/pi
@@ -290,13 +299,13 @@ __device__ __forceinline__ SinCosPart sincos_issue_scaled(const MathTables& T, d
   o.ca = row[1];
   const double r2 = r * r;
   double ps = -h * h2 * h2 * h2 / 5040.0;
-  ps = fma(ps, r2, h * h2 * h2 / 120.0);
-  ps = fma(ps, r2, -h * h2 / 6.0);
-  ps = fma(ps, r2, h);
+  ps = fma_k(ps, r2, h * h2 * h2 / 120.0);
+  ps = fma_k(ps, r2, -h * h2 / 6.0);
+  ps = fma_k(ps, r2, h);
   o.sr = r * ps;
   double pc = -h2 * h2 * h2 / 720.0;
-  pc = fma(pc, r2, h2 * h2 / 24.0);
-  pc = fma(pc, r2, -0.5 * h2);
+  pc = fma_k(pc, r2, h2 * h2 / 24.0);
+  pc = fma_k(pc, r2, -0.5 * h2);
   o.cr = fma(r2, pc, 1.0);
   return o;
 }
@@ -310,11 +319,11 @@ __device__ __forceinline__ ExpPart exp_part_scaled(const MathTables& T, double t
   o.m = ni >> 6;
   o.tj = ((const lds_double*)(&T.e2[0]))[ni & 63];
   double p = h * h * h * h * h / 120.0;
-  p = fma(p, r, h * h * h * h / 24.0);
-  p = fma(p, r, h * h * h / 6.0);
-  p = fma(p, r, 0.5 * h * h);
-  p = fma(p, r, h);
-  o.p = fma(p, r, 1.0);
+  p = fma_k(p, r, h * h * h * h / 24.0);
+  p = fma_k(p, r, h * h * h / 6.0);
+  p = fma_k(p, r, 0.5 * h * h);
+  p = fma_k(p, r, h);
+  o.p = fma_k(p, r, 1.0);
   return o;
 }
 // e^(c v ln2/64), clamped like exp_issue (in units of ln2/64).
@@ -333,8 +342,8 @@ __device__ __forceinline__ ExpPart exp_issue_bounded(const MathTables& T, double
 // cos x for |x| <= 2^-8 (to x^5 and x^4, truncation 2^-68 and 2^-57).
 __device__ __forceinline__ double exp_small(double x) {
   double p = fma(x, 1.0 / 720.0, 1.0 / 120.0);
-  p = fma(p, x, 1.0 / 24.0);
-  p = fma(p, x, 1.0 / 6.0);
+  p = fma_k(p, x, 1.0 / 24.0);
+  p = fma_k(p, x, 1.0 / 6.0);
   p = fma(p, x, 0.5);
   p = fma(p, x, 1.0);
   return fma(p, x, 1.0);

@@ -60,7 +60,7 @@ inline int bucket_of(int N) {
 struct KernelArgs {
   // work list of one launch (launch order)
   const int32_t* wu_item;
-  // split tail units: points | node groups << 16 per unit
+  // value units and split gradient units: points | node groups << 16 per unit
   const int32_t* wu_split;
   const int32_t* wu_p0;
   const int64_t* wu_rec;
@@ -119,8 +119,7 @@ struct ReduceArgs {
 hipError_t launch_item_consts(int precision, const int64_t* row_off, const double* layers,
                               double* rec, float* recf, int n_items, hipStream_t st);
 // precision: NR_F64 or NR_F32
-hipError_t launch_forward(int precision, int op, bool split, const KernelArgs& a, int n_wu,
-                          hipStream_t st);
+hipError_t launch_forward(int precision, int op, const KernelArgs& a, int n_wu, hipStream_t st);
 // store: the store variant (only for buckets within store_max_layers)
 // Forms of the gradient kernel: the recompute form, the store form (buckets up
 // to the precision's store limit), and the recompute form that also
@@ -133,7 +132,7 @@ enum GradForm { kFormRecompute = 0, kFormStore = 1, kFormRecomputeRes = 2, kForm
 enum WuMode { kModeFull = 0, kModeTail = 1, kModeSplit = 2 };
 hipError_t launch_grad(int precision, int bucket, int form, int mode, const KernelArgs& a,
                        int n_wu, hipStream_t st);
-hipError_t launch_forward_f32(int op, bool split, const KernelArgs& a, int n_wu, hipStream_t st);
+hipError_t launch_forward_f32(int op, const KernelArgs& a, int n_wu, hipStream_t st);
 hipError_t launch_grad_f32(int bucket, int form, int mode, const KernelArgs& a, int n_wu,
                            hipStream_t st);
 // Deep buckets (index >= kFirstDeepBucket): one object per (precision,

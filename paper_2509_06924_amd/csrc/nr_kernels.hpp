@@ -285,35 +285,6 @@ __device__ __forceinline__ cx<typename P::real> fronting_kz(double q) {
   return mk(static_cast<Re>(0.5 * q), Re(0));
 }
 
-// ---------------------------------------------------------------------------
-// Forward-only reflectivity of one node (no state kept; runtime layer loop).
-// ---------------------------------------------------------------------------
-template <class P>
-__device__ __forceinline__ double node_reflectivity(const MathTables& T, const Layers<P>& L, int N,
-                                                    double q) {
-  using Re = typename P::real;
-  using Cx = cx<Re>;
-  const double kz0sq = kz0_squared(q);
-  Cx kzn = medium_root(L, kz0sq, N + 1).kz;
-  Cx Pv = mk(Re(1), Re(0)), Qv = mk(Re(0), Re(0));
-  for (int jj = N; jj >= 1; --jj) {
-    const Cx kzc = medium_root(L, kz0sq, jj).kz;
-    const Iface<Re> it = interface_coeffs(T, kzc, kzn, L.Nr(jj), L.Ni(jj), L.C(jj));
-    const Cx Pn = cmul_add(it.rp, Qv, Pv);
-    const Cx t = cmul_add(it.rp, Pv, Qv);
-    Qv = layer_phase(T, kzc, L.D(jj)) * t;
-    Pv = Pn;
-    kzn = kzc;
-  }
-  {
-    const Iface<Re> it = interface_coeffs(T, fronting_kz<P>(q), kzn, L.Nr(0), L.Ni(0), L.C(0));
-    const Cx Pn = cmul_add(it.rp, Qv, Pv);
-    Qv = cmul_add(it.rp, Pv, Qv);
-    Pv = Pn;
-  }
-  return (double)cabs2(Qv * crecip(Pv));
-}
-
 // Shared WU prologue.
 struct WuInfo {
   int item, ds, N, nq, i;
@@ -415,67 +386,6 @@ __device__ __forceinline__ void flag(int32_t* status, int item, uint32_t bits) {
     atomicOr(reinterpret_cast<unsigned int*>(status + item), bits);
 }
 
-// ---------------------------------------------------------------------------
-// Smeared R of a forward unit's point.  SPLIT: the unit holds npts points of
-// one item and lane g npts + p evaluates point p on the nodes g, g + G, ...;
-// the point's G lanes then add their partial sums, so that every one of them
-// holds the point's smeared R (split_setup).
-// ---------------------------------------------------------------------------
-template <class P, bool SPLIT>
-__device__ __forceinline__ double forward_point(const KernelArgs& a, const Shared& s,
-                                                const WuInfo& u, const SplitInfo& sp, int lane,
-                                                bool& badq) {
-  const int K = u.smeared ? kSmearNodes : 1;
-  const int k0 = SPLIT ? (u.active ? sp.g : K) : 0;
-  const int kstep = SPLIT ? sp.G : 1;
-  double Rsm = 0.0;
-  badq = !(u.Q > 0.0);
-  for (int k = k0; k < K; k += kstep) {
-    const double q = (K == 1) ? u.Q : smear_at(u.Q, u.sig, ld(s.t[k]));
-    badq |= !(q > 0.0);
-    const double wk = (K == 1) ? 1.0 : ld(s.w[k]);
-    Rsm += wk * node_reflectivity(s.tab, item_layers<P>(a, u.roff, u.N, k), u.N, q);
-  }
-  if constexpr (SPLIT) {
-    double tot = 0.0;
-    int bq = 0;
-    for (int gg = 0; gg < sp.G; ++gg) {
-      const int src = gg * sp.npts + lane % sp.npts;
-      tot += __shfl(Rsm, src, 64);
-      bq |= __shfl(badq ? 1 : 0, src, 64);
-    }
-    Rsm = tot;
-    badq = bq != 0;
-  }
-  return Rsm;
-}
-
-// ---------------------------------------------------------------------------
-// R_hat per point (nr_reflectivity).
-// ---------------------------------------------------------------------------
-template <class P, bool SPLIT = false>
-__global__ __launch_bounds__(64) void k_reflectivity(KernelArgs a) {
-  __shared__ Shared s;
-  const int lane = threadIdx.x;
-  const int w = blockIdx.x;
-  SplitInfo sp{0, 1, 64};
-  const WuInfo u = SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
-  stage_shared(s, lane, a.rule);
-  bool badq = false;
-  const double Rsm = forward_point<P, SPLIT>(a, s, u, sp, lane, badq);
-  if (u.active && sp.g == 0) {
-    double Rhat = a.scale[u.item] * Rsm + a.bkg[u.item];
-    uint32_t bits = 0;
-    if (badq) {
-      Rhat = __builtin_nan("");
-      bits |= kItemBadQ;
-    }
-    if (!isfinite(Rhat)) bits |= kItemNonfinite;
-    flag(a.item_status, u.item, bits);
-    a.out[a.out_off[u.item] + u.i] = Rhat;
-  }
-}
-
 // Log-likelihood term of one point; sets status bits.
 __device__ __forceinline__ double point_loglik(double Rhat, double Robs, double e, bool badq,
                                                uint32_t& bits) {
@@ -486,30 +396,6 @@ __device__ __forceinline__ double point_loglik(double Rhat, double Robs, double 
   if (bits) ll = __builtin_nan("");
   if (!isfinite(ll)) bits |= kItemNonfinite;
   return ll;
-}
-
-// ---------------------------------------------------------------------------
-// logL partial per WU (nr_loglik): record = 1 double.
-// ---------------------------------------------------------------------------
-template <class P, bool SPLIT = false>
-__global__ __launch_bounds__(64) void k_loglik(KernelArgs a) {
-  __shared__ Shared s;
-  const int lane = threadIdx.x;
-  const int w = blockIdx.x;
-  SplitInfo sp{0, 1, 64};
-  const WuInfo u = SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
-  stage_shared(s, lane, a.rule);
-  bool badq = false;
-  const double Rsm = forward_point<P, SPLIT>(a, s, u, sp, lane, badq);
-  double ll = 0.0;
-  uint32_t bits = 0;
-  if (u.active && sp.g == 0) {
-    const double Rhat = a.scale[u.item] * Rsm + a.bkg[u.item];
-    ll = point_loglik(Rhat, a.r_obs[u.qoff + u.i], a.r_err[u.qoff + u.i], badq, bits);
-  }
-  flag(a.item_status, u.item, bits);
-  ll = wave_sum(ll);
-  if (lane == 0) a.rec[a.wu_rec[w]] = ll;
 }
 
 // ---------------------------------------------------------------------------
@@ -1313,23 +1199,6 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
 // Launchers of one precision (instantiated in nr_kernels_f64.hip and
 // nr_kernels_f32.hip).
 // ---------------------------------------------------------------------------
-template <class P>
-hipError_t launch_forward_p(int op, bool split, const KernelArgs& a, int n_wu, hipStream_t st) {
-  if (n_wu <= 0) return hipSuccess;
-  if (op == kOpReflectivity) {
-    if (split)
-      hipLaunchKernelGGL((k_reflectivity<P, true>), dim3(n_wu), dim3(64), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_reflectivity<P, false>), dim3(n_wu), dim3(64), 0, st, a);
-  } else {
-    if (split)
-      hipLaunchKernelGGL((k_loglik<P, true>), dim3(n_wu), dim3(64), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_loglik<P, false>), dim3(n_wu), dim3(64), 0, st, a);
-  }
-  return hipGetLastError();
-}
-
 // Launch of one gradient bucket; BUCKETS is the list macro of the buckets
 // this translation unit compiles.
 #define NR_LAUNCH(LM, S, RES)                                                                 \
