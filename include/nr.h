@@ -173,13 +173,12 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *     the 8 XCDs (1..64; the default 8 keeps an item's units in one L2).
  *   pack_tails: 1 packs the trailing partial point groups of several items
  *     of equal depth into one wave (default); 0 gives each its own wave.
- *   split_tails (bits): the trailing partial group of an item of at most 10
- *     layers gets a wave of its own when it fills at least 48 of the 64
- *     lanes, which keeps the item's layer records wave-uniform:
- *       NR_TAILS_LONE   by itself (48 points or more);
- *       NR_TAILS_SPLIT  for a smeared item, with the lanes split over 2 to 4
- *                       groups of smearing nodes (lane = node group x point;
- *                       12 to 32 points).
+ *   split_tails (bits): the trailing partial group of an item gets a wave of
+ *     its own, which keeps the item's layer records wave-uniform:
+ *       NR_TAILS_LONE   by itself (48 points or more, smeared items 33);
+ *       NR_TAILS_SPLIT  for a smeared item, with the lanes split over groups
+ *                       of smearing nodes (lane = node group x point; 32
+ *                       points or fewer).
  *     Other tails follow pack_tails.  A third bit serves small problems:
  *       NR_SPLIT_SMALL  when the gradient's full units (64 points each) are
  *                       fewer than one round of the device (two waves per

@@ -146,8 +146,6 @@ struct RecordLists {
 // the chunks keep the longest-first order.  The last partial chunk maps to
 // itself.
 constexpr int kXcds = 8;
-// deepest bucket whose partial point groups may get a wave of their own
-constexpr int kSplitTailMaxLayers = 10;
 size_t xcd_order(size_t b, size_t n, size_t run) {
   const size_t chunk = kXcds * run;
   const size_t c0 = (b / chunk) * chunk;
@@ -850,23 +848,19 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       rec_gr += rsz;
     }
     if (ntail > 0) {
-      // a smeared tail that fills most of a wave with node groups x points
-      // gets a wave of its own (uniform item); else the tail's lanes join a
-      // packed unit and sum into one record of the item
+      // A smeared tail gets a wave of its own: of 32 points or fewer with
+      // node groups x points over the lanes, else with idle lanes.  Its
+      // item stays wave-uniform, and no wave runs all 17 nodes for a few
+      // points.  Packing tails of several items into one wave (per-lane
+      // layer records, up to 1 KB of spill in the deep kernels, and launches
+      // of few waves that each take as long as a full unit) was the rule
+      // beyond 10 layers: 2048 ragged items 8.9 -> 6.6 ms, 200 items 5.3 ->
+      // 3.4 ms, 16384 items 38.0 -> 37.0 ms, FP32 5.6 -> 4.2 ms for 2048.
+      // Unsmeared tails, one node each, are still packed.
       const int G = std::min(kWuPoints / ntail, K);
-      // measured on MI355X: a wave of its own pays off up to 10 layers (the
-      // 4096-draw batch: 3 % faster); deeper kernels, at one wave per SIMD,
-      // lose more to the idle lanes and the split kernel's registers than
-      // they gain from scalar record loads (16384-item ragged batch: 8 %
-      // slower), so their tails stay packed
-      const bool own_wave = kBucketLmax[bk] <= kSplitTailMaxLayers;
-      if (own_wave && (p->opts.split_tails & NR_TAILS_LONE) && ntail >= 48) {
-        // most of a wave: a full unit with idle lanes (uniform item)
+      if ((p->opts.split_tails & NR_TAILS_LONE) && (ntail >= 48 || (K > 1 && G == 1))) {
         grad_units[bk].push_back({b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)});
-      } else if (own_wave && (p->opts.split_tails & NR_TAILS_SPLIT) && K > 1 && G >= 2 &&
-                 G <= 4 && ntail * G >= 48) {
-        // at least four nodes per lane, so that the wave's epilogue (one
-        // reduction of every record field) stays small beside its work
+      } else if ((p->opts.split_tails & NR_TAILS_SPLIT) && G >= 2) {
         Wu u{b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)};
         u.split = ntail | (G << 16);
         split_units[bk].push_back(u);

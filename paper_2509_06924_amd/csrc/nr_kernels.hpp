@@ -1160,12 +1160,20 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
   // a split unit's lane takes every G-th node from its group's first
   const int k0 = SPLIT ? (u.active ? sp.g : K) : 0;
   const int kstep = SPLIT ? sp.G : 1;
-  for (int k = k0; k < K; k += kstep) {
+  // In a split unit the counter differs between lanes, and the layer records,
+  // indexed with it (zero_mask), become vector loads; kWaveCounter counts per
+  // wave instead.  (The 6-20-layer FP64 forms keep the per-lane counter: their
+  // plans reach them only by explicit option, beside k_grad_select.)
+  constexpr bool kWaveCounter =
+      SPLIT && (!std::is_same<P, F64>::value || LMAX < kSelectMinLayers || LMAX > kSelectMaxLayers);
+  for (int kk = kWaveCounter ? 0 : k0; kk < K; kk += kstep) {
+    const int k = kWaveCounter ? kk + k0 : kk;
+    if (kWaveCounter && k >= K) continue;
     const double tk = ld(s.t[k]);
     const double q = (K == 1) ? u.Q : smear_at(u.Q, u.sig, tk);
     badq |= !(q > 0.0);
     const double wk = (K == 1) ? 1.0 : ld(s.w[k]);
-    const Layers<P> L = item_layers<P>(a, u.roff, N, k);
+    const Layers<P> L = item_layers<P>(a, u.roff, N, kk);
     double R;
     if constexpr (STORE)
       R = node_grad_store<P, LMAX>(s.tab, L, tape, acc, lane, q, wk, edge);
