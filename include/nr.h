@@ -180,24 +180,23 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *                       of smearing nodes (lane = node group x point; 32
  *                       points or fewer).
  *     Other tails follow pack_tails.  A third bit serves small problems:
- *       NR_SPLIT_SMALL  when the gradient's full units (64 points each) are
- *                       fewer than one round of the device (two waves per
- *                       SIMD), every point group of a smeared item of at most
- *                       NR_MAX_LAYERS layers is split the same way, over
- *                       G = min(17, round / units) node groups, so that a
- *                       single fit spreads over many waves.
+ *       NR_SPLIT_SMALL  when the gradient's units of 64 points are fewer
+ *                       than six per SIMD of the device, every point group
+ *                       of a smeared item of at most NR_MAX_LAYERS layers is
+ *                       split the same way, over the G of 1, 2, 3, 4, 6, 9 or
+ *                       17 node groups that finishes first by a measured
+ *                       model, so that a single fit spreads over many waves;
+ *                       the value calls split below three units per SIMD.
  *     Default: all three bits.
- *   side_stream: 1 (default) runs every second full-unit launch of the
- *     gradient (one launch per layer-count bucket) and its tail and split
- *     launches that hold at most one round of the device (two waves per
- *     SIMD of every compute unit) on a second stream that the plan owns
- *     (default priority, non-blocking), forked from the caller's stream
- *     after the per-layer constants and joined back before the reduction:
- *     small launches run beside the full-unit launches instead of leaving
- *     most of the device idle after them, and consecutive buckets overlap;
+ *   side_stream: 1 (default) spreads the gradient's launches (one per
+ *     layer-count bucket and kind of unit) over the caller's stream and up to
+ *     three more that the plan owns (default priority, non-blocking), forked
+ *     from the caller's stream after the per-layer constants and joined back
+ *     before the reduction: small launches run beside others instead of
+ *     leaving most of the device idle, and consecutive ones overlap;
  *     0 keeps every launch on the caller's stream.  The fork and join are
  *     event waits, so calls stay ordered on the caller's stream and can be
- *     captured into a HIP graph (the side stream joins the capture).  Calls
+ *     captured into a HIP graph (the side streams join the capture).  Calls
  *     on one plan from several host threads are serialised around the fork
  *     and join.
  *   node_groups: the (sample, Q) tiling of the gradient's work units.  0

@@ -164,6 +164,8 @@ inline int default_store_layers(int precision) { return precision == NR_F32 ? 8 
 // at 18 and 20, within 1 % at 24-32, 4 % slower at 40 (nr_select.hpp).  Up to 4
 // layers the store form stays.
 constexpr int kSelectMinLayers = 6, kSelectMaxLayers = 20;
+// Waves per SIMD that the gradient kernels of a bucket run at.
+int grad_waves_per_simd(int precision, int lmax);
 hipError_t launch_reduce(int op, const ReduceArgs& a, hipStream_t st);
 // Allows the gradient reduction its dynamic LDS for records of max_rows media.
 hipError_t prepare_reduce(int max_rows);

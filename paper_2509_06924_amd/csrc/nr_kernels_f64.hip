@@ -296,6 +296,10 @@ hipError_t launch_grad(int precision, int bucket, int form, int mode, const Kern
                              : launch_grad_shallow<F64>(bucket, form, mode, a, n_wu, st);
 }
 
+int grad_waves_per_simd(int precision, int lmax) {
+  return precision == NR_F32 ? F32::min_waves(lmax, false) : F64::min_waves(lmax, false);
+}
+
 hipError_t prepare_reduce(int max_rows) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_reduce_grad),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
