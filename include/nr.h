@@ -580,6 +580,17 @@ nr_status nr_vi_elbo_grad(const nr_plan* plan, const nr_values* data, const nr_v
 nr_status nr_tie_sum(int64_t n_out, const int64_t* first, const int64_t* src, const double* in,
                      double* out, void* stream);
 
+/* Per-item scaling of a gradient, for a caller whose objective is a function
+ * of the items' logL (reverse mode: seed[b] = d objective / d logL_b):
+ *   out_rows[entry of item b] = seed_b g_rows[entry],
+ *   out_inst[0][b] = seed_b g_inst[b][0], out_inst[1][b] = seed_b g_inst[b][1],
+ * seed_b = seed[b * seed_stride] (0: one value for all).  Device arrays;
+ * out_inst holds 2 * n_items values.  NR_EINVAL for a NULL pointer, a negative
+ * stride or a plan of another device. */
+nr_status nr_scale_gradient(const nr_plan* plan, const double* g_rows, const double* g_inst,
+                            const double* seed, int64_t seed_stride, double* out_rows,
+                            double* out_inst, void* stream);
+
 /* Optional timing hooks for profiling: while set, every evaluation call
  * records `start` (a hipEvent_t owned by the caller) on its stream just
  * before its first layer-product kernel and `stop` just after its last one,

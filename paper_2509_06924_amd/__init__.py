@@ -122,7 +122,8 @@ class Plan:
 
 
 def _dp(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    """Device pointer of a tensor (as an int), or None."""
+    return t.data_ptr() if t is not None else None
 
 
 def _values(q, r_obs, r_err, layers, scale, bkg, item_status=None, dq=None, dqq_item=None):
@@ -131,9 +132,13 @@ def _values(q, r_obs, r_err, layers, scale, bkg, item_status=None, dq=None, dqq_
 
 
 def _stream(stream):
+    """Raw handle of a torch stream, or of the current device's current stream
+    (asked for directly: building a torch.cuda.Stream object takes 3 of the
+    20 us of a small call)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def nr_reflectivity(plan, values, r_hat, workspace=None, stream=None):
@@ -617,6 +622,32 @@ def tie_map_to_csr(tie_of_entry, n_out):
     return first, src.astype(np.int64)
 
 
+def _plain(problem, g_rows, g_inst, grad_out):
+    """Whether nr_scale_gradient may take these tensors as they are."""
+    import torch
+    return (problem.plan.handle is not None
+            and all(type(t) is torch.Tensor and t.dtype == torch.float64
+                    and t.device == problem.device for t in (g_rows, g_inst, grad_out))
+            and g_rows.is_contiguous() and g_inst.is_contiguous()
+            and g_rows.shape == problem.layers.shape
+            and g_inst.shape == (problem.plan.n_items, 2)
+            and grad_out.shape == (problem.plan.n_items,)
+            and torch.cuda.current_device() == problem.device.index)
+
+
+def _scale_gradient(problem, g_rows, g_inst, grad_out):
+    """Gradients of sum_b grad_out_b logL_b in one launch."""
+    import torch
+    n = problem.plan.n_items
+    out = torch.empty_like(g_rows)
+    inst = torch.empty(2, n, dtype=torch.float64, device=problem.device)
+    stride = grad_out.stride(0) if n > 1 else 1
+    _n.check(_n.lib().nr_scale_gradient(problem.plan.handle, _dp(g_rows), _dp(g_inst),
+                                        _dp(grad_out), stride, _dp(out), _dp(inst),
+                                        _stream(None)))
+    return out, inst[0], inst[1]
+
+
 def _make_autograd():
     import torch
 
@@ -634,7 +665,7 @@ def _make_autograd():
                                                            scale.detach().contiguous(),
                                                            bkg.detach().contiguous())
                 ctx.save_for_backward(g_rows, g_inst)
-                ctx.row_item = problem.row_item
+                ctx.problem = problem
             else:
                 logL = problem.loglik(layers.detach().contiguous(), scale.detach().contiguous(),
                                       bkg.detach().contiguous())
@@ -643,7 +674,12 @@ def _make_autograd():
         @staticmethod
         def backward(ctx, grad_out):
             g_rows, g_inst = ctx.saved_tensors
-            go_rows = grad_out[ctx.row_item].unsqueeze(1)
+            problem = ctx.problem
+            if not torch.is_grad_enabled() and _plain(problem, g_rows, g_inst, grad_out):
+                return (*_scale_gradient(problem, g_rows, g_inst, grad_out), None)
+            # (a graph of the backward is being built, or a hook handed back
+            # something else than was saved)
+            go_rows = grad_out[problem.row_item].unsqueeze(1)
             return g_rows * go_rows, g_inst[:, 0] * grad_out, g_inst[:, 1] * grad_out, None
 
     class NRReflectivity(torch.autograd.Function):
@@ -684,13 +720,16 @@ NRReflectivity = _LazyAutograd(1)
 
 
 def _row_item(problem):
+    """The item of each row (device), made on first use."""
     import torch
-    ro = problem.plan.row_off
-    idx = np.repeat(np.arange(problem.plan.n_items), np.diff(ro))
-    return torch.as_tensor(idx, dtype=torch.int64, device=problem.device)
+    if "_row_item" not in problem.__dict__:
+        ro = problem.plan.row_off
+        idx = np.repeat(np.arange(problem.plan.n_items), np.diff(ro))
+        problem._row_item = torch.as_tensor(idx, dtype=torch.int64, device=problem.device)
+    return problem._row_item
 
 
-Problem.row_item = property(lambda self: self.__dict__.setdefault("_row_item", _row_item(self)))
+Problem.row_item = property(_row_item)
 
 
 def pack_theta(theta, sld_unit=1.0):

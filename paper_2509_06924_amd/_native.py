@@ -223,6 +223,8 @@ def lib():
                                   ctypes.POINTER(PlanOptions), P, P]
         L.nr_tie_sum.restype = ctypes.c_int32
         L.nr_tie_sum.argtypes = [ctypes.c_int64, P, P, P, P, P]
+        L.nr_scale_gradient.restype = ctypes.c_int32
+        L.nr_scale_gradient.argtypes = [P, P, P, P, ctypes.c_int64, P, P, P]
         L.nr_loglik_grad_noalloc.restype = ctypes.c_int32
         L.nr_loglik_grad_noalloc.argtypes = [P, ctypes.POINTER(Values), P, P, P, P]
         L.nr_smearing_rule.restype = ctypes.c_int32

@@ -1488,6 +1488,19 @@ nr_status nr_tie_sum(int64_t n_out, const int64_t* first, const int64_t* src, co
   return e == hipSuccess ? NR_OK : hip_fail(e, "tie-sum launch");
 }
 
+nr_status nr_scale_gradient(const nr_plan* p, const double* g_rows, const double* g_inst,
+                            const double* seed, int64_t seed_stride, double* out_rows,
+                            double* out_inst, void* stream) {
+  int dev = -1;
+  if (!p || seed_stride < 0 || hipGetDevice(&dev) != hipSuccess || dev != p->device)
+    return NR_EINVAL;
+  if (p->n_items == 0) return NR_OK;
+  if (!g_rows || !g_inst || !seed || !out_rows || !out_inst) return NR_EINVAL;
+  hipError_t e = launch_scale_gradient(p->n_items, p->d_row_off, g_rows, g_inst, seed, seed_stride,
+                                       out_rows, out_inst, (hipStream_t)stream);
+  return e == hipSuccess ? NR_OK : hip_fail(e, "gradient scaling launch");
+}
+
 nr_status nr_plan_set_timing_events(nr_plan* p, void* start, void* stop) {
   if (!p || ((start == nullptr) != (stop == nullptr))) return NR_EINVAL;
   p->ev_start = static_cast<hipEvent_t>(start);

@@ -161,6 +161,20 @@ __global__ __launch_bounds__(256) void k_tie_sum(int64_t n_out, const int64_t* f
   out[k] = s;
 }
 
+// One wave per item: its gradient times its seed (nr_scale_gradient).  One
+// launch instead of the index, two selects and three products of tensor
+// operations, whose host time is what bounds a small fit's backward pass.
+__global__ __launch_bounds__(64) void k_scale_gradient(const int64_t* row_off, const double* g_rows,
+                                                       const double* g_inst, const double* seed,
+                                                       int64_t seed_stride, double* out_rows,
+                                                       double* out_inst) {
+  const int64_t b = blockIdx.x;
+  const double s = seed[b * seed_stride];
+  const int64_t e1 = 4 * row_off[b + 1];
+  for (int64_t e = 4 * row_off[b] + threadIdx.x; e < e1; e += 64) out_rows[e] = g_rows[e] * s;
+  if (threadIdx.x < 2) out_inst[threadIdx.x * (int64_t)gridDim.x + b] = g_inst[2 * b + threadIdx.x] * s;
+}
+
 static dim3 grid_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
 hipError_t launch_kick(int64_t n_row_entries, int64_t n_inst, double* mom_rows,
@@ -201,6 +215,15 @@ hipError_t launch_vi_reduce(int64_t n_samples, int P, int rows, const double* om
   hipLaunchKernelGGL(k_vi_reduce, dim3((unsigned)(P / kViEntries + 1)),
                      dim3(kViEntries * kViLanes), 0, st, n_samples, P, rows, omega, mask, eps, logL,
                      g_rows, g_inst, grad_mu, grad_omega, elbo);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_gradient(int32_t n_items, const int64_t* row_off, const double* g_rows,
+                                 const double* g_inst, const double* seed, int64_t seed_stride,
+                                 double* out_rows, double* out_inst, hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_scale_gradient, dim3(n_items), dim3(64), 0, st, row_off, g_rows, g_inst,
+                     seed, seed_stride, out_rows, out_inst);
   return hipGetLastError();
 }
 

@@ -190,6 +190,9 @@ hipError_t launch_vi_reduce(int64_t n_samples, int P, int rows, const double* om
                             const uint8_t* mask, const double* eps, const double* logL,
                             const double* g_rows, const double* g_inst, double* grad_mu,
                             double* grad_omega, double* elbo, hipStream_t st);
+hipError_t launch_scale_gradient(int32_t n_items, const int64_t* row_off, const double* g_rows,
+                                 const double* g_inst, const double* seed, int64_t seed_stride,
+                                 double* out_rows, double* out_inst, hipStream_t st);
 hipError_t launch_tie_sum(int64_t n_out, const int64_t* first, const int64_t* src,
                           const double* in, double* out, hipStream_t st);
 
