@@ -190,15 +190,15 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *     Default: all three bits.
  *   side_stream: 1 (default) spreads the gradient's launches (one per
  *     layer-count bucket and kind of unit) over the caller's stream and up to
- *     three more that the plan owns (default priority, non-blocking), forked
+ *     three more (default priority, non-blocking; one set per device, shared
+ *     by its plans, and a set of the plan's own for captured calls), forked
  *     from the caller's stream after the per-layer constants and joined back
  *     before the reduction: small launches run beside others instead of
  *     leaving most of the device idle, and consecutive ones overlap;
  *     0 keeps every launch on the caller's stream.  The fork and join are
  *     event waits, so calls stay ordered on the caller's stream and can be
  *     captured into a HIP graph (the side streams join the capture).  Calls
- *     on one plan from several host threads are serialised around the fork
- *     and join.
+ *     from several host threads are serialised around the fork and join.
  *   node_groups: the (sample, Q) tiling of the gradient's work units.  0
  *     (default) follows the rules above (64 points per wave, each lane
  *     running all 17 nodes of its point, except the split units); 2..17 puts

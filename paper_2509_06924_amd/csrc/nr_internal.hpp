@@ -116,7 +116,9 @@ struct ReduceArgs {
   int32_t max_rows;  // the largest rows of any item (record length)
 };
 
-hipError_t launch_item_consts(int precision, const int64_t* row_off, const double* layers,
+// What the constants kernel writes beside the double records.
+enum ConstsKind { kConstsPlain, kConstsFloat, kConstsScaled };
+hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const double* layers,
                               double* rec, float* recf, int n_items, hipStream_t st);
 // precision: NR_F64 or NR_F32
 hipError_t launch_forward(int precision, int op, const KernelArgs& a, int n_wu, hipStream_t st);
@@ -160,10 +162,13 @@ inline int store_max_layers(int precision) {
 // (10 layers: 0.56 vs 0.60); FP32 store wins up to 8 layers.
 inline int default_store_layers(int precision) { return precision == NR_F32 ? 8 : 4; }
 // Buckets whose default is the select form (FP64; packed tail units take the
-// recompute form): 4-7 % faster than the recompute form at 6-16 layers, 1-2 %
-// at 18 and 20, within 1 % at 24-32, 4 % slower at 40 (nr_select.hpp).  Up to 4
-// layers the store form stays.
-constexpr int kSelectMinLayers = 6, kSelectMaxLayers = 20;
+// recompute form): 6-9 % faster than the recompute form at 6-20 layers
+// (nr_select.hpp); 24-32 layers 7 % and 36 layers 4 % where the batch has no
+// other bucket of that depth, but 16384 ragged items 0.7 % (up to 28 layers) to
+// 2.3 % (up to 36) slower, two such kernels running side by side; 40 layers
+// 10 % slower.  Up to 4 layers the store form stays (11 % faster at 1 layer,
+// 8 % at 4).
+constexpr int kSelectMinLayers = 6, kSelectMaxLayers = 20, kSelectAloneLayers = 36;
 // Waves per SIMD that the gradient kernels of a bucket run at.
 int grad_waves_per_simd(int precision, int lmax);
 hipError_t launch_reduce(int op, const ReduceArgs& a, hipStream_t st);

@@ -19,7 +19,7 @@ hipError_t NR_DEEP_LAUNCHER(NR_PREC, NR_BUCKET_LMAX)(int form, int mode, const K
   constexpr int LM = NR_BUCKET_LMAX;
   if (n_wu <= 0) return hipSuccess;
   if (form == kFormSelect) {
-    if constexpr (std::is_same<P, F64>::value && LM <= kSelectMaxLayers) {
+    if constexpr (std::is_same<P, F64>::value && LM <= kSelectAloneLayers) {
       if (mode == kModeTail) return hipErrorInvalidValue;
       NR_SELECT_LAUNCH(LM)
       return hipGetLastError();

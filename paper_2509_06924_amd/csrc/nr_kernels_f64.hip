@@ -42,9 +42,10 @@ __device__ __forceinline__ double scaled_const(double ch, double cl, double hi, 
 }
 
 // One block of 64 per item, lanes over the media: the item's layer records
-// (doubles), and the second array of the precision: EXT (FP64 plans) the
-// scaled exponent factors and the item's range of kz0^2 for the above-edge
-// node form (see LevelRecords), else (FP32) the float copies.
+// (doubles), and a second array: none, float copies (FP32), or the scaled
+// exponent factors and the item's range of kz0^2 for the above-edge node form
+// (see LevelRecords; its reductions take 1.3 us, a tenth of a small call, so
+// FP64 launches that do not read it go without).
 //
 // The range [lo, hi] of kz0^2 in which every medium propagates and absorbs
 // little enough for the above-edge form, from bounds that hold for any stack:
@@ -54,9 +55,10 @@ __device__ __forceinline__ double scaled_const(double ch, double cl, double hi, 
 //   |C_m Im(kz_m kz_m+1)| <= 2.1 |C_m| (B_m + B_m+1) <= 2^-8   sincos_small
 //   |C_m Re(kz_m kz_m+1)| <= 1.01 |C_m| (kz0^2 - min A) <= 1e7  exp_issue_bounded
 // A NaN or an infinity in the rows fails a comparison and empties the range.
-template <bool EXT>
+template <ConstsKind KIND>
 __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, const double* layers,
                                                     double* rec, float* recf, int n_items) {
+  constexpr bool EXT = KIND == kConstsScaled;
   const int b = blockIdx.x;
   if (b >= n_items) return;
   const int64_t r0 = row_off[b];
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
                       -2.1 * v[4] * (B + bn) <= 0x1p-8 && fabs(v[5]) < 1e12;
       lo = fmax(lo, ok ? A + need : __builtin_inf());
       hi = fmin(hi, amin - 9.9e6 / fmin(v[4], -1e-200));
-    } else {
+    } else if constexpr (KIND == kConstsFloat) {
       float* outf = recf + (r0 + m) * kRecFloats;
       for (int f = 0; f < 5; ++f) outf[f] = (float)v[f + 1];
       for (int f = 5; f < kRecFloats; ++f) outf[f] = 0.0f;
@@ -257,15 +259,13 @@ __global__ __launch_bounds__(1024) void k_reduce_grad(ReduceArgs a) {
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_item_consts(int precision, const int64_t* row_off, const double* layers,
+hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const double* layers,
                               double* rec, float* recf, int n_items, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  if (precision == NR_F32)
-    hipLaunchKernelGGL(k_item_consts<false>, dim3(n_items), dim3(64), 0, st, row_off, layers, rec,
-                       recf, n_items);
-  else
-    hipLaunchKernelGGL(k_item_consts<true>, dim3(n_items), dim3(64), 0, st, row_off, layers, rec,
-                       recf, n_items);
+  const auto k = kind == kConstsFloat    ? k_item_consts<kConstsFloat>
+                 : kind == kConstsScaled ? k_item_consts<kConstsScaled>
+                                         : k_item_consts<kConstsPlain>;
+  hipLaunchKernelGGL(k, dim3(n_items), dim3(64), 0, st, row_off, layers, rec, recf, n_items);
   return hipGetLastError();
 }
 

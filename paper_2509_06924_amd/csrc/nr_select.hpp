@@ -21,15 +21,17 @@
 // 5.4 in k_loglik_grad.
 //
 // Measured on MI355X against k_loglik_grad (2048 draws x 448 points, 5 %
-// dQ/Q, about 0.6 of the nodes above; one box):
-//   layers        6     8     10    12    14    16    18    20
-//   before, us    819   1067  1375  1724  2038  2377  2660  3057
-//   after, us     774   1006  1321  1623  1980  2292  2624  2993
-// 4096 draws x 10 layers x 400 points 2.51 -> 2.36 ms.  From 24 layers on the
-// two bodies (100 KB and more) crowd the instruction cache that two compute
-// units share: 24-32 layers within 1 %, 40 layers 4 % slower, and the ragged
-// 16384-item batch 5 % slower with the form at every depth, against unchanged
-// with it up to 20.  Packed tail units spilled up to 1 KB here and stay with
+// dQ/Q, about 0.6 of the nodes above; one box, us):
+//   layers   6     8     10    12    14    16    18    20    24    28    32    36
+//   before   790   1033  1340  1680  1987  2381  2666  3061  3790  4567  5416  6625
+//   after    724   946   1238  1531  1886  2196  2509  2865  3528  4246  5075  6373
+// 4096 draws x 10 layers x 400 points 2.42 -> 2.25 ms.  The two bodies (100 KB
+// and more from 24 layers on) crowd the instruction cache that two compute
+// units share, so units in flight together should run the same form: ordered
+// by their place in the data set instead of item by item, 16-20 layers gained
+// 4-5 % (28 layers item by item: 200 cache misses a wave against 13, a seventh
+// of its time).  40 layers run 10 % slower (464 B of spill beside 200 KB of
+// code).  Packed tail units spilled up to 1 KB here and stay with
 // k_loglik_grad, and so do the resolution form and FP32 (whose exponentials
 // are hardware functions).
 #pragma once
