@@ -219,6 +219,7 @@ struct nr_plan {
   nr_plan_options opts;
   int bucket_form[kNumBuckets];  // GradForm of the plain gradient
   bool grad_scaled = false;      // a gradient launch takes the select form
+  bool scan_select = false;      // the deep items' launches do
   std::vector<int64_t> q_off, row_off, out_off;
   std::vector<int32_t> dataset_of_item;
   std::vector<double> dqq;
@@ -425,9 +426,14 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
                        bool res) {
   {
     // the value kernels and the select form read the scaled factors
-    const bool scaled = op != kOpLoglikGrad || (p->grad_scaled && !res);
+    const bool grad_scaled = op == kOpLoglikGrad && p->grad_scaled && !res;
     hipError_t e = launch_item_consts(
-        p->precision == NR_F32 ? kConstsFloat : scaled ? kConstsScaled : kConstsPlain, p->d_row_off,
+        p->precision == NR_F32   ? kConstsFloat
+        : op != kOpLoglikGrad    ? kConstsScaled
+        : !grad_scaled           ? kConstsPlain
+        : p->scan_select         ? kConstsScan
+                                 : kConstsScaled,
+        p->d_row_off,
         a.layers, const_cast<double*>(a.consts), const_cast<float*>(a.constsf), p->n_items, st);
     if (e != hipSuccess) return hip_fail(e, "constants launch");
   }
@@ -475,7 +481,8 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     if (!grad)
       launch_err = launch_forward(p->precision, op, a, L.n_wu, ls);
     else if (L.bucket == kDeepBucket)
-      launch_err = launch_grad_scan(res, L.scan_ch, a, L.n_wu, ls);
+      launch_err = form == kFormSelect ? launch_grad_scan_select(L.scan_ch, a, L.n_wu, ls)
+                                       : launch_grad_scan(res, L.scan_ch, a, L.n_wu, ls);
     else
       launch_err = launch_grad(p->precision, L.bucket, form, mode, a, L.n_wu, ls);
     if (launch_err != hipSuccess) break;
@@ -1171,7 +1178,11 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       }
       Launch L;
       L.bucket = std::min(bk, kDeepBucket);
-      L.form = bk < kNumBuckets ? p->bucket_form[bk] : kFormRecompute;
+      // (deep items: the scan kernel that the deepest bucket's option names;
+      // the records of an FP32 plan have no room for the scaled factors)
+      const bool scan_select = p->precision == NR_F64 &&
+                               p->opts.grad_variant[kNumBuckets - 1] == NR_VARIANT_AUTO;
+      L.form = bk < kNumBuckets ? p->bucket_form[bk] : scan_select ? kFormSelect : kFormRecompute;
       L.scan_ch = bk >= kDeepBucket ? std::max(scan_ch[bk - kDeepBucket], 1) : 0;
       L.split = split;
       L.n_wu = (int)v.size();
@@ -1201,7 +1212,10 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   make_full(kOpLoglikGrad, grad_units, p->launches_grad, false);
   make_full(kOpLoglikGrad, split_units, p->launches_grad, true);
   p->launches_grad.insert(p->launches_grad.end(), tail_launches.begin(), tail_launches.end());
-  for (const Launch& L : p->launches_grad) p->grad_scaled |= L.form == kFormSelect;
+  for (const Launch& L : p->launches_grad) {
+    p->grad_scaled |= L.form == kFormSelect;
+    p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
+  }
   // A launch that does not fill the device, or the last waves of one that
   // does, leave it idle until the next launch of their stream; launches on
   // other streams fill it.  The longest launches come first, each on the

@@ -117,7 +117,9 @@ struct ReduceArgs {
 };
 
 // What the constants kernel writes beside the double records.
-enum ConstsKind { kConstsPlain, kConstsFloat, kConstsScaled };
+// (kConstsScan: as kConstsScaled, deep items in the order of the scan kernel of
+// nr_scan_select.hip)
+enum ConstsKind { kConstsPlain, kConstsFloat, kConstsScaled, kConstsScan };
 hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const double* layers,
                               double* rec, float* recf, int n_items, hipStream_t st);
 // precision: NR_F64 or NR_F32
@@ -177,6 +179,8 @@ hipError_t prepare_reduce(int max_rows);
 // The scan kernel for items deeper than kMaxLayers: one wave per (item,
 // point) unit, ch_max = the largest levels-per-lane of the launch's items.
 hipError_t launch_grad_scan(bool res, int ch_max, const KernelArgs& a, int n_wu, hipStream_t st);
+// The same without the resolution form, on the scaled factors (nr_scan_select.hip).
+hipError_t launch_grad_scan_select(int ch_max, const KernelArgs& a, int n_wu, hipStream_t st);
 size_t scan_lds_bytes(int ch_max);
 // Allows the scan kernels their dynamic LDS (over 64 KB for deep chunks).
 hipError_t prepare_grad_scan(int ch_max);

@@ -58,7 +58,7 @@ __device__ __forceinline__ double scaled_const(double ch, double cl, double hi, 
 template <ConstsKind KIND>
 __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, const double* layers,
                                                     double* rec, float* recf, int n_items) {
-  constexpr bool EXT = KIND == kConstsScaled;
+  constexpr bool EXT = KIND == kConstsScaled || KIND == kConstsScan;
   const int b = blockIdx.x;
   if (b >= n_items) return;
   const int64_t r0 = row_off[b];
@@ -77,6 +77,13 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
     amin = -wave_max(-amin);
   }
   double lo = 1e-30, hi = 1e300;
+  // the scan kernel's order (see LaneRecords in nr_scan_select.hip): the six
+  // doubles per slot fit the item's 6 + 4 per row, of which slots take four
+  // and two, for any deep item (CH LN <= NR + CH - 1 slots, CH <= 8)
+  const bool scan = KIND == kConstsScan && NR - 2 > kMaxLayers;
+  const int ch64 = (NR - 1 + 63) / 64;
+  const int nt = 64 * (ch64 <= 8 ? 1 : ch64 <= 16 ? 2 : 4);
+  const int CH = (NR - 1 + nt - 1) / nt, LN = (NR + CH - 1) / CH;
   for (int m = threadIdx.x; m < NR; m += 64) {
     double v[kRecDoubles];
     const double A = Af(m), B = Bf(m);
@@ -97,18 +104,35 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
     }
     // the fronting and backing have no thickness (their rows' d is ignored)
     v[5] = (m == 0 || m + 1 == NR) ? 0.0 : 2.0 * rows[4 * m];
-    double* out = rec + (r0 + m) * kRecDoubles;
-    for (int f = 0; f < kRecDoubles; ++f) out[f] = v[f];
+    if (!scan) {
+      double* out = rec + (r0 + m) * kRecDoubles;
+      for (int f = 0; f < kRecDoubles; ++f) out[f] = v[f];
+    }
     if constexpr (EXT) {
       // 64/pi and 64/ln 2 as sums of two doubles
       constexpr double kPiLo = -1.259435307211679e-15, kLn2Lo = 1.3027375194195861e-15;
-      double* ext = reinterpret_cast<double*>(recf) + (r0 + m) * kExtDoubles;
-      if (m > 0) {
-        ext[0] = scaled_const(v[5], 0.0, k64OverPi, kPiLo);
-        ext[1] = scaled_const(v[5], 0.0, k64OverLn2, kLn2Lo);
+      const double pd = scaled_const(v[5], 0.0, k64OverPi, kPiLo);
+      const double lc = scaled_const(v[4], -2.0 * sg2_lo, k64OverLn2, kLn2Lo);
+      if (scan) {
+        const int slot = (m % CH) * LN + m / CH;
+        double* ab = rec + r0 * kRecDoubles + 2 * slot;
+        double* nn = ab + 2 * CH * LN;
+        double* pl = reinterpret_cast<double*>(recf) + r0 * kExtDoubles + 2 * slot;
+        ab[0] = A;
+        ab[1] = B;
+        nn[0] = v[2];
+        nn[1] = v[3];
+        pl[0] = pd;
+        pl[1] = lc;
+      } else {
+        double* ext = reinterpret_cast<double*>(recf) + (r0 + m) * kExtDoubles;
+        if (m > 0) {
+          ext[0] = pd;
+          ext[1] = scaled_const(v[5], 0.0, k64OverLn2, kLn2Lo);
+        }
+        ext[2] = scaled_const(v[4], -2.0 * sg2_lo, k64OverPi, kPiLo);
+        ext[3] = lc;
       }
-      ext[2] = scaled_const(v[4], -2.0 * sg2_lo, k64OverPi, kPiLo);
-      ext[3] = scaled_const(v[4], -2.0 * sg2_lo, k64OverLn2, kLn2Lo);
       const double db = 32.0 * v[5] * B;
       const double need = fmax(fmax(256.0 * B, db * db), (amax - amin) * (1.0 / 15.0));
       const double bn = (m + 1 < NR) ? Bf(m + 1) : 0.0;
@@ -128,6 +152,7 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
     hi = -wave_max(-hi);
     if (threadIdx.x == 0) {
       double* ext = reinterpret_cast<double*>(recf) + r0 * kExtDoubles;
+      if (scan) ext += NR * kExtDoubles - 2;
       ext[0] = lo;
       ext[1] = hi;
     }
@@ -264,6 +289,7 @@ hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const dou
   if (n_items <= 0) return hipSuccess;
   const auto k = kind == kConstsFloat    ? k_item_consts<kConstsFloat>
                  : kind == kConstsScaled ? k_item_consts<kConstsScaled>
+                 : kind == kConstsScan   ? k_item_consts<kConstsScan>
                                          : k_item_consts<kConstsPlain>;
   hipLaunchKernelGGL(k, dim3(n_items), dim3(64), 0, st, row_off, layers, rec, recf, n_items);
   return hipGetLastError();

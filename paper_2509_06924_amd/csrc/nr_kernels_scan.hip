@@ -26,46 +26,11 @@
 // lanes; the lower lane's part is kept in an extra slot and added to the
 // upper lane's slot before the record is written.  Every level's arithmetic
 // is that of the shallow kernels (same helpers), in FP64.
-#include "nr_kernels.hpp"
+#include "nr_scan.hpp"
 
 namespace nr {
 
 namespace {
-
-struct M2 {
-  cd a, b, c, d;  // [[a, b], [c, d]]
-};
-
-__device__ __forceinline__ M2 m2_mul(const M2& x, const M2& y) {
-  M2 z;
-  z.a = x.a * y.a + x.b * y.c;
-  z.b = x.a * y.b + x.b * y.d;
-  z.c = x.c * y.a + x.d * y.c;
-  z.d = x.c * y.b + x.d * y.d;
-  return z;
-}
-
-__device__ __forceinline__ M2 m2_identity() {
-  M2 z;
-  z.a = mk(1.0, 0.0);
-  z.b = mk(0.0, 0.0);
-  z.c = mk(0.0, 0.0);
-  z.d = mk(1.0, 0.0);
-  return z;
-}
-
-__device__ __forceinline__ cd shfl_cd(cd v, int src) {
-  return mk(__shfl(v.re, src, 64), __shfl(v.im, src, 64));
-}
-
-__device__ __forceinline__ M2 shfl_m2(const M2& m, int src) {
-  M2 z;
-  z.a = shfl_cd(m.a, src);
-  z.b = shfl_cd(m.b, src);
-  z.c = shfl_cd(m.c, src);
-  z.d = shfl_cd(m.d, src);
-  return z;
-}
 
 // Level jj's coefficients from kz_jj (kzc) and medium jj + 1's root.
 struct Lvl {
@@ -97,31 +62,6 @@ __device__ __forceinline__ RootT<double> rec_root(const Layers<F64>::Rec& r, dou
 }
 
 }  // namespace
-
-// Per-lane storage of the state tape (the state entering each of the lane's
-// levels; between steps 1 and 3, the level's r' and e) and of the
-// accumulators (Hw re, Hw im, Hd, Hs per medium slot; slot t is medium lo + t,
-// slot n = hi - lo the lane's lower boundary medium): registers, or LDS in
-// planes interleaved over the NT lanes of a data point.
-template <int CHT, bool IN_LDS, int NT>
-struct LaneTape {
-  double r[IN_LDS ? 1 : CHT][4];
-  __device__ __forceinline__ double& at(double* lds, int gl, int t, int f) {
-    if constexpr (IN_LDS)
-      return lds[(t * 4 + f) * NT + gl];
-    else
-      return r[t][f];
-  }
-};
-
-__device__ __forceinline__ M2 load_m2(const cd* x) {
-  M2 z;
-  z.a = x[0];
-  z.b = x[1];
-  z.c = x[2];
-  z.d = x[3];
-  return z;
-}
 
 // CHT: the largest levels-per-lane the launch's items need (1, 2, 4 or 8);
 // NW: waves per data point (1, 2 or 4).
@@ -440,21 +380,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_loglik_grad_scan(KernelArgs a) {
     rec[2] = ghat;
     if (RES) rec[3 + 4 * NR] = fac * hq;
   }
-}
-
-// The configuration of a launch whose deepest item needs ch64 levels per
-// lane at 64 lanes: one wave per data point up to 8 levels per lane, else two
-// or four waves, so that no lane holds more than 8 levels (the tape then fits
-// 2 KB of LDS per level and wave, and the kernel two waves per SIMD); the
-// levels per lane round up to a power of two.
-static int scan_nw(int ch64) { return ch64 <= 8 ? 1 : ch64 <= 16 ? 2 : 4; }
-
-static int scan_cht(int ch64) {
-  const int nw = scan_nw(ch64);
-  const int ch = (ch64 + nw - 1) / nw;
-  int c = 1;
-  while (c < ch) c <<= 1;
-  return c;
 }
 
 size_t scan_lds_bytes(int ch_max) {
