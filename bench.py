@@ -92,6 +92,10 @@ KERNEL_SOURCES = ["paper_2509_06924_amd/csrc/nr_kernels.hpp",
                   "paper_2509_06924_amd/csrc/nr_kernels_f32.hip",
                   "paper_2509_06924_amd/csrc/nr_kernels_bucket.hip",
                   "paper_2509_06924_amd/csrc/nr_kernels_scan.hip",
+                  "paper_2509_06924_amd/csrc/nr_select.hpp",
+                  "paper_2509_06924_amd/csrc/nr_scan.hpp",
+                  "paper_2509_06924_amd/csrc/nr_scan_select.hip",
+                  "paper_2509_06924_amd/csrc/nr_value.hpp",
                   "paper_2509_06924_amd/csrc/nr_device.hpp",
                   "paper_2509_06924_amd/csrc/nr_internal.hpp",
                   "paper_2509_06924_amd/build.py"]
@@ -171,7 +175,7 @@ def record_counters(csv_dir, workload, precision, command):
             name = r["Kernel_Name"]
             if "k_item_consts" in name:
                 consts.add(r["Dispatch_Id"])
-            if "k_loglik_grad" in name:
+            if "k_loglik_grad" in name or "k_grad_" in name:
                 c = r["Counter_Name"]
                 vals[c] = vals.get(c, 0.0) + float(r["Counter_Value"])
     if not consts:
