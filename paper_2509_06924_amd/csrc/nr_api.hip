@@ -119,6 +119,7 @@ struct Launch {
   int form = kFormRecompute;  // gradient: the kernel form (resolution calls take their own)
   bool tail = false;
   bool split = false;  // split tail units (one item's partial group, lanes over node groups)
+  bool one = false;    // split units of one node per lane, for the per-lane node counter
   int scan_ch = 0;     // deep lists: the largest levels-per-lane of its items at 64 lanes
   int side = 0;        // 0: the caller's stream, k: the plan's side stream k - 1
   double est = 0.0;    // gradient: estimated time (see launch_estimate)
@@ -354,11 +355,17 @@ size_t op_doubles(const nr_plan* p, int op) {
 // wait).  e and s1 are fits of measured calls (MI355X, 7 to 7168 units of 64
 // points at every G): 0.6 and 1.4 for the kernels at two waves per SIMD (10
 // layers), 1.35 and 1.16 at one (24 layers), whose levels cost 1.26 as much.
+// FP32 nodes are shorter beside the same epilogue, e = 2, and two to three
+// waves take as long as 3.3 (20 to 4000 units of 5, 12, 20 and 26 layers).
 double launch_estimate(int precision, int lmax, int64_t waves, int nodes, int64_t simds) {
   const bool one_wave = grad_waves_per_simd(precision, lmax) == 1;
-  const double e = one_wave ? 1.35 : 0.6, s1 = one_wave ? 1.16 : 1.4;
+  const bool f32 = precision == NR_F32 && !one_wave;
+  const double e = f32 ? 2.0 : one_wave ? 1.35 : 0.6, s1 = one_wave ? 1.16 : 1.4;
   const double w = (double)waves / (double)simds;
-  const double f = w <= 1.0 ? s1 : w <= 2.0 ? 2.1 : w <= 4.0 ? w + 0.6 : w + 0.2;
+  const double f = w <= 1.0              ? s1
+                   : w <= 2.0            ? 2.1
+                   : f32 || w <= 4.0     ? std::max(f32 ? 3.3 : 0.0, w + 0.6)
+                                         : w + 0.2;
   return f * (nodes + e) * (lmax + 1) * (one_wave ? 1.26 : 1.0);
 }
 
@@ -394,7 +401,7 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
   const size_t limit = std::max<size_t>(count(G_fit), NR_NOALLOC_SCRATCH_BYTES);
   double best = 0.0;
   int best_G = 1;
-  for (int G : {1, 2, 3, 4, 6, 9, 17}) {
+  for (int G : {1, 2, 3, 4, 5, 6, 9, 17}) {
     if (count(G) > limit) continue;
     const int nodes = (kSmearNodes + G - 1) / G;
     int launches = 0;
@@ -408,8 +415,9 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
       work += one / 5.2 * ((double)waves[k] / (double)simds);
     }
     const double t = std::max(sum / std::min(std::max(launches, 1), 1 + kSideStreams), work);
-    // (5 % in favour of whole nodes: their kernels are the faster ones)
-    if (best == 0.0 || t < best * (best_G == 1 ? 0.95 : 1.0)) {
+    // (5 % in favour of whole nodes in FP64: their kernels are the faster ones; FP32,
+    // 1500 units of 12 layers: 145 us whole, 128 in two groups)
+    if (best == 0.0 || t < best * (best_G == 1 && p->precision == NR_F64 ? 0.95 : 1.0)) {
       best = t;
       best_G = G;
     }
@@ -476,7 +484,10 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     a.tail_pt = L.lane_pt;
     a.tail_rec = L.lane_rec;
     const int form = res ? kFormRecomputeRes : L.form;
-    const int mode = L.tail ? kModeTail : L.split ? kModeSplit : kModeFull;
+    const int mode = L.tail              ? kModeTail
+                     : L.one && !res     ? kModeSplitOne
+                     : L.split           ? kModeSplit
+                                         : kModeFull;
     const hipStream_t ls = (fork && L.side > 0) ? side[L.side - 1] : st;
     if (!grad)
       launch_err = launch_forward(p->precision, op, a, L.n_wu, ls);
@@ -924,22 +935,34 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   int small_G = 1, small_G_fwd = 1;
   if (p->opts.split_tails & NR_SPLIT_SMALL) {
     int64_t units = 0, units_fwd = 0;
+    bool smeared = true;  // every shallow item
     for (int b = 0; b < nI; ++b) {
       const int s = p->dataset_of_item[b];
       const int N = (int)(p->row_off[b + 1] - p->row_off[b]) - 2;
       const int64_t u = (p->q_off[s + 1] - p->q_off[s] + kWuPoints - 1) / kWuPoints;
       units_fwd += u;
-      if (bucket_of(N) != kDeepBucket) units += u;
+      if (bucket_of(N) == kDeepBucket) continue;
+      units += u;
+      smeared &= p->dqq[s] > 0.0;
     }
     if (units > 0 && units < kSmallPlanWaves * simds)
       small_G = pick_node_groups(p, units, simds);
+    // One node per lane, a wave alone on its SIMD: it waits for each scalar record
+    // load of the two node forms.  The one-form kernels, whose constants are cheaper
+    // too (us a call, two forms / one: 10 items of 180 points, 6 layers 24.6 /
+    // 23.1, 18 layers 39.3 / 36.7, 36 layers 76.5 / 68.6).
+    if (small_G == kSmearNodes && smeared)
+      for (int& form : p->bucket_form)
+        if (form == kFormSelect) form = kFormRecompute;
     // Value units, by how many each SIMD would get unsplit.  Measured on MI355X
     // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
     // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
     // 113 / 92 / 98 / 102; 2688: 147 / 130 / 137 / 139; 3584: 152 / 160 / 174 /
-    // 178.  G = 4 and 17 leave lanes or nodes over and are never the best.
+    // 178.  G = 4 leaves nodes over and is never the best; G = 17 is as long as
+    // its waves find a SIMD each: 38 units of 12 layers 20.9 us at 9, 16.4 at 17.
     if (units_fwd > 0)
-      small_G_fwd = 5 * units_fwd < 2 * simds   ? 9
+      small_G_fwd = 24 * units_fwd <= simds     ? 17
+                    : 4 * units_fwd < simds     ? 9
                     : 2 * units_fwd < 3 * simds ? 6
                     : units_fwd < 3 * simds     ? 2
                                                 : 1;
@@ -1078,8 +1101,10 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   {
     std::vector<std::vector<int32_t>> b_item(kNumBuckets), b_litem(kNumBuckets), b_lpt(kNumBuckets);
     std::vector<std::vector<int64_t>> b_lrec(kNumBuckets);
+    int b_nodes[kNumBuckets] = {};
     for (auto& kv : tails) {
       const int bk = bucket_of(kv.first.first);
+      b_nodes[bk] = std::max(b_nodes[bk], kv.first.second);
       auto& v = kv.second;
       std::stable_sort(v.begin(), v.end(),
                        [](const Tail& x, const Tail& y) { return x.count > y.count; });
@@ -1135,7 +1160,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       L.form = p->bucket_form[bk] == kFormSelect ? kFormRecompute : p->bucket_form[bk];
       L.tail = true;
       L.n_wu = (int)b_item[bk].size();
-      L.est = launch_estimate(p->precision, kBucketLmax[bk], L.n_wu, kSmearNodes, simds);
+      L.est = launch_estimate(p->precision, kBucketLmax[bk], L.n_wu, b_nodes[bk], simds);
       e = upload(&L.item, b_item[bk]);
       keep(L.item);
       if (e == hipSuccess) { e = upload(&L.lane_item, b_litem[bk]); keep(L.lane_item); }
@@ -1193,6 +1218,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         const int G = std::max(1, u.split >> 16);
         nodes = std::max(nodes, (K + G - 1) / G);
       }
+      L.one = split && nodes == 1 && L.form == kFormRecompute && L.bucket != kDeepBucket &&
+              kBucketLmax[L.bucket] >= kOneNodeLayers;
       L.est = L.bucket == kDeepBucket
                   ? 1.5 * 8 * nodes * L.n_wu * std::max(1, L.scan_ch / 8) / (double)simds
                   : launch_estimate(p->precision, kBucketLmax[L.bucket], L.n_wu, nodes, simds);

@@ -52,6 +52,7 @@ namespace nr {
 // min_waves(LMAX): the waves per SIMD the gradient kernel is compiled for (its
 // register budget is 512 / min_waves per lane).
 struct F64 {
+  static constexpr bool kLaneCounter = false;
   using real = double;
   static constexpr int kStoreMax = kStoreMaxLayers;
   static constexpr int kSlimMax = 6;
@@ -88,6 +89,7 @@ struct F64 {
   }
 };
 struct F32 {
+  static constexpr bool kLaneCounter = false;
   using real = float;
   static constexpr int kStoreMax = kStoreMaxLayersF32;
   static constexpr int kSlimMax = 0;
@@ -1121,6 +1123,17 @@ __device__ __forceinline__ void write_grad_record(const KernelArgs& a, const WuI
 //   [3 + 3NR + m]  sum Re(conj(ubar) kz_{m-1} kz_m)   (sigma_m factor applied later)
 //   [3 + 4NR]      d/d(dQ/Q) (relative resolution)
 // ---------------------------------------------------------------------------
+// The precision with nodes counted per lane in split units.  A wave alone on
+// its SIMD that runs one node waits for each scalar load of a record it has
+// not read yet; the per-lane counter's vector loads run ahead.  One item of 200
+// points, 26 layers FP32: 50.3 -> 43.4 us a call; 7 items of 178 points, 38
+// layers FP64: 80.1 -> 71.3 us.  With more waves or nodes the scalar loads are the
+// faster ones (500 items, 26 layers FP32: 678 us per lane, 529 per wave).
+template <class P>
+struct PerLane : P {
+  static constexpr bool kLaneCounter = true;
+};
+
 template <class P, int LMAX, bool STORE, bool TAIL, bool RES, bool SPLIT = false>
 __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void k_loglik_grad(
     KernelArgs a) {
@@ -1162,10 +1175,14 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
   const int kstep = SPLIT ? sp.G : 1;
   // In a split unit the counter differs between lanes, and the layer records,
   // indexed with it (zero_mask), become vector loads; kWaveCounter counts per
-  // wave instead.  (The 6-20-layer FP64 forms keep the per-lane counter: their
-  // plans reach them only by explicit option, beside k_grad_select.)
+  // wave instead.  The 6-20-layer FP64 forms (beside k_grad_select: by explicit
+  // option, or at one node per lane) and the 8-12-layer FP32 ones keep the
+  // per-lane counter: 10 items of 180 points, 10 layers FP32 26.9 us a call per
+  // wave, 24.8 per lane; 40 items of 300 points, 41.5 / 38.8; at 6 layers 26.1 / 27.3.
   constexpr bool kWaveCounter =
-      SPLIT && (!std::is_same<P, F64>::value || LMAX < kSelectMinLayers || LMAX > kSelectMaxLayers);
+      SPLIT && !P::kLaneCounter &&
+      (std::is_same<P, F64>::value ? LMAX < kSelectMinLayers || LMAX > kSelectMaxLayers
+                                   : LMAX < 8 || LMAX > 12);
   for (int kk = kWaveCounter ? 0 : k0; kk < K; kk += kstep) {
     const int k = kWaveCounter ? kk + k0 : kk;
     if (kWaveCounter && k >= K) continue;

@@ -29,10 +29,26 @@ static hipError_t launch_select_shallow(int bucket, int mode, const KernelArgs& 
   return hipErrorInvalidValue;
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// Rotations within the rows of 16 lanes (row_ror 8, 4, 2, 1), then the four
+// rows: six exchanges through LDS hardware, one after the other, take longer
+// than the rest of a small k_item_consts.  All 64 lanes have to be active.
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
+  v = fmax(v, dpp_move<0x128>(v));
+  v = fmax(v, dpp_move<0x124>(v));
+  v = fmax(v, dpp_move<0x122>(v));
+  v = fmax(v, dpp_move<0x121>(v));
+  return fmax(fmax(lane_value(v, 0), lane_value(v, 16)),
+              fmax(lane_value(v, 32), lane_value(v, 48)));
 }
 
 // c (hi + lo), rounded once; c = ch + cl.

@@ -105,6 +105,7 @@ __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
   const int w = blockIdx.x;
   SplitInfo sp;
   const WuInfo u = split_setup(a, w, lane, sp);
+  if (std::is_same<P, F64>::value && sp.G > 1) warm_records(a, u.roff, u.N, lane);
   stage_shared(s, lane, a.rule);
   const int K = u.smeared ? kSmearNodes : 1;
   bool badq = !(u.Q > 0.0);
