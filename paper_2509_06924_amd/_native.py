@@ -32,7 +32,7 @@ EXPORTS = ("nr_version", "nr_status_string", "nr_plan_create", "nr_plan_destroy"
            "nr_loglik_grad_res", "nr_hmc_create", "nr_hmc_destroy", "nr_hmc_init",
            "nr_hmc_transition", "nr_hmc_graph_create", "nr_hmc_adapt", "nr_vi_mvn_create",
            "nr_vi_mvn_destroy", "nr_vi_mvn_step", "nr_vi_mvn_graph_create", "nr_autotune",
-           "nr_smearing_rule", "nr_loglik_grad_noalloc")
+           "nr_smearing_rule", "nr_loglik_grad_noalloc", "nr_scale_gradient")
 
 
 class BatchDesc(ctypes.Structure):

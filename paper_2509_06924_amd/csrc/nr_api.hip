@@ -352,19 +352,25 @@ size_t op_doubles(const nr_plan* p, int op) {
 // epilogue (one reduction per record field) worth e nodes, and w waves per
 // SIMD take f(w) times one wave's share of a full SIMD: s1 alone (nothing
 // hides its latencies), 2.1 up to two, then a little over w (the last wave's
-// wait).  e and s1 are fits of measured calls (MI355X, 7 to 7168 units of 64
+// wait), but not over two rounds of two up to four (676 items of 355 points, 12
+// layers, 3.96 waves: 480 us whole, 546 in three groups).  e and s1 are fits of measured calls (MI355X, 7 to 7168 units of 64
 // points at every G): 0.6 and 1.4 for the kernels at two waves per SIMD (10
-// layers), 1.35 and 1.16 at one (24 layers), whose levels cost 1.26 as much.
-// FP32 nodes are shorter beside the same epilogue, e = 2, and two to three
+// layers), 1.35 and 1.16 at one (24 layers), whose levels cost 1.26 as much
+// and whose split waves go round by round (24 layers, G = 2, 2.5 / 3.2 / 3.7 /
+// 4.4 / 5.2 / 6.4 waves per SIMD take 3.1 / 4.2 / 4.1 / 5.0 / 6.0 / 7.0).
+// Shallow (676 items of 355 points, 1 layer: 64.6 whole, 71 / 73 / 106 us at G =
+// 2 / 3 / 9) and FP32 nodes are shorter beside the same epilogue, e = 2; in FP32 two to three
 // waves take as long as 3.3 (20 to 4000 units of 5, 12, 20 and 26 layers).
 double launch_estimate(int precision, int lmax, int64_t waves, int nodes, int64_t simds) {
   const bool one_wave = grad_waves_per_simd(precision, lmax) == 1;
   const bool f32 = precision == NR_F32 && !one_wave;
-  const double e = f32 ? 2.0 : one_wave ? 1.35 : 0.6, s1 = one_wave ? 1.16 : 1.4;
+  const double e = f32 || lmax < kSelectMinLayers ? 2.0 : one_wave ? 1.35 : 0.6, s1 = one_wave ? 1.16 : 1.4;
   const double w = (double)waves / (double)simds;
   const double f = w <= 1.0              ? s1
                    : w <= 2.0            ? 2.1
-                   : f32 || w <= 4.0     ? std::max(f32 ? 3.3 : 0.0, w + 0.6)
+                   : one_wave            ? (nodes < kSmearNodes ? std::ceil(w) : w + 0.2)
+                   : f32                 ? std::max(3.3, w + 0.6)
+                   : w <= 4.0            ? std::min(w + 0.6, 4.2)
                                          : w + 0.2;
   return f * (nodes + e) * (lmax + 1) * (one_wave ? 1.26 : 1.0);
 }
@@ -394,12 +400,17 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
       const int64_t npts = deep ? 1 : p->dqq[s] > 0.0 ? kWuPoints / G : kWuPoints;
       const int64_t n = (p->q_off[s + 1] - p->q_off[s] + npts - 1) / npts;
       doubles += (size_t)n * (4 + 4 * (size_t)rows);
-      if (!deep) waves[bk] += n;
+      if (deep) continue;
+      // (FP32: a short tail beside whole units runs its share of the nodes: 710
+      // items of 262 points, 26 layers 839 us whole, 1041 in two groups)
+      const int64_t tail = (p->q_off[s + 1] - p->q_off[s]) % kWuPoints;
+      const bool part = p->precision == NR_F32 && G == 1 && tail > 0 && tail <= kWuPoints / 4;
+      waves[bk] += part ? n - 1 : n;
     }
     return sizeof(double) * doubles;
   };
   const size_t limit = std::max<size_t>(count(G_fit), NR_NOALLOC_SCRATCH_BYTES);
-  double best = 0.0;
+  double best = 0.0, whole = 1.0;
   int best_G = 1;
   for (int G : {1, 2, 3, 4, 5, 6, 9, 17}) {
     if (count(G) > limit) continue;
@@ -410,14 +421,17 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
       if (waves[k] == 0) continue;
       ++launches;
       const double t = launch_estimate(p->precision, kBucketLmax[k], waves[k], nodes, simds);
+      // in favour of whole nodes, whose kernels are the faster ones in FP64: 8 %, and
+      // 10 % at one wave per SIMD (2877 units of 24 layers 844 us whole, 887 in two
+      // groups); in FP32, 1500 units of 12 layers, 145 whole, 128 in two groups
+      if (G == 1 && p->precision == NR_F64)
+        whole = std::min(whole, grad_waves_per_simd(NR_F64, kBucketLmax[k]) == 1 ? 0.9 : 0.92);
       const double one = launch_estimate(p->precision, kBucketLmax[k], 5 * simds, nodes, simds);
       sum += t;
       work += one / 5.2 * ((double)waves[k] / (double)simds);
     }
     const double t = std::max(sum / std::min(std::max(launches, 1), 1 + kSideStreams), work);
-    // (5 % in favour of whole nodes in FP64: their kernels are the faster ones; FP32,
-    // 1500 units of 12 layers: 145 us whole, 128 in two groups)
-    if (best == 0.0 || t < best * (best_G == 1 && p->precision == NR_F64 ? 0.95 : 1.0)) {
+    if (best == 0.0 || t < best * (best_G == 1 ? whole : 0.98)) {
       best = t;
       best_G = G;
     }
@@ -935,25 +949,15 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   int small_G = 1, small_G_fwd = 1;
   if (p->opts.split_tails & NR_SPLIT_SMALL) {
     int64_t units = 0, units_fwd = 0;
-    bool smeared = true;  // every shallow item
     for (int b = 0; b < nI; ++b) {
       const int s = p->dataset_of_item[b];
       const int N = (int)(p->row_off[b + 1] - p->row_off[b]) - 2;
       const int64_t u = (p->q_off[s + 1] - p->q_off[s] + kWuPoints - 1) / kWuPoints;
       units_fwd += u;
-      if (bucket_of(N) == kDeepBucket) continue;
-      units += u;
-      smeared &= p->dqq[s] > 0.0;
+      if (bucket_of(N) != kDeepBucket) units += u;
     }
     if (units > 0 && units < kSmallPlanWaves * simds)
       small_G = pick_node_groups(p, units, simds);
-    // One node per lane, a wave alone on its SIMD: it waits for each scalar record
-    // load of the two node forms.  The one-form kernels, whose constants are cheaper
-    // too (us a call, two forms / one: 10 items of 180 points, 6 layers 24.6 /
-    // 23.1, 18 layers 39.3 / 36.7, 36 layers 76.5 / 68.6).
-    if (small_G == kSmearNodes && smeared)
-      for (int& form : p->bucket_form)
-        if (form == kFormSelect) form = kFormRecompute;
     // Value units, by how many each SIMD would get unsplit.  Measured on MI355X
     // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
     // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
@@ -969,6 +973,31 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   }
   // a tiling given by the caller: every point group split over node_groups
   if (p->opts.node_groups >= 2) small_G = p->opts.node_groups;
+  // Where every lane runs one node, the two node forms do not pay for their
+  // costlier constants and the scalar record loads that a wave waits for at its
+  // first node: the one-form kernels.  us a call, two forms / one: 10 smeared items
+  // of 180 points, 6 layers 24.6 / 23.1, 18 layers 39.3 / 36.7, 36 layers 76.5 /
+  // 68.6; unsmeared, 10 items of 180 points, 10 layers 24.8 / 23.6, 4000 of 400
+  // 264 / 261, 1000 of 400, 32 layers 341 / 323, 3544 of 784, 21 layers 1394 / 1353.
+  // The scan kernel of deep items likewise, up to two points per SIMD: 6 items of
+  // 96 points, 306 layers 31.7 / 29.0, 22 of 84, 459 layers 63.7 / 61.1, but 100
+  // of 300, 200 layers 207.6 / 235.0.
+  bool one_node = true, scan_one_node = true;
+  int64_t scan_points = 0;
+  for (int b = 0; b < nI; ++b) {
+    const int s = p->dataset_of_item[b];
+    const bool smeared = p->dqq[s] > 0.0;
+    if (bucket_of((int)(p->row_off[b + 1] - p->row_off[b]) - 2) == kDeepBucket) {
+      scan_one_node &= !smeared;
+      scan_points += p->q_off[s + 1] - p->q_off[s];
+    } else {
+      one_node &= !smeared || small_G == kSmearNodes;
+    }
+  }
+  scan_one_node &= scan_points <= 2 * simds;
+  if (one_node)
+    for (int& form : p->bucket_form)
+      if (form == kFormSelect) form = kFormRecompute;
   for (int b = 0; b < nI; ++b) {
     const int s = p->dataset_of_item[b];
     const int64_t nq = p->q_off[s + 1] - p->q_off[s];
@@ -1205,7 +1234,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       L.bucket = std::min(bk, kDeepBucket);
       // (deep items: the scan kernel that the deepest bucket's option names;
       // the records of an FP32 plan have no room for the scaled factors)
-      const bool scan_select = p->precision == NR_F64 &&
+      const bool scan_select = p->precision == NR_F64 && !scan_one_node &&
                                p->opts.grad_variant[kNumBuckets - 1] == NR_VARIANT_AUTO;
       L.form = bk < kNumBuckets ? p->bucket_form[bk] : scan_select ? kFormSelect : kFormRecompute;
       L.scan_ch = bk >= kDeepBucket ? std::max(scan_ch[bk - kDeepBucket], 1) : 0;
