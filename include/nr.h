@@ -161,8 +161,15 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  * beyond rounding order; they select among equivalent schedules:
  *   grad_variant[k] for layer-count bucket k (nr_bucket_lmax(k) layers):
  *     NR_VARIANT_AUTO       the library's default for the bucket: the store
- *                           form up to 4 layers in NR_F64 and 8 in NR_F32,
- *                           the recompute form deeper (the faster on MI355X);
+ *                           form up to 4 layers in NR_F64 and 8 in NR_F32;
+ *                           for smeared NR_F64 items of 6 to 20 layers (36 where
+ *                           one bucket of the plan is deeper than 20) the
+ *                           recompute form with a node form for points above
+ *                           every critical edge; else the recompute form.
+ *                           Beyond NR_MAX_LAYERS the deepest bucket's entry:
+ *                           AUTO the scan with determinants (NR_F64, smeared or
+ *                           more than two points per SIMD), else the scan with
+ *                           prefix products;
  *     NR_VARIANT_STORE      forward sweep keeps states, phases and interface
  *                           coefficients for the adjoint (only buckets of at
  *                           most nr_store_max_layers(precision) layers);
@@ -183,7 +190,7 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *       NR_SPLIT_SMALL  when the gradient's units of 64 points are fewer
  *                       than six per SIMD of the device, every point group
  *                       of a smeared item of at most NR_MAX_LAYERS layers is
- *                       split the same way, over the G of 1, 2, 3, 4, 6, 9 or
+ *                       split the same way, over the G of 1, 2, 3, 4, 5, 6, 9 or
  *                       17 node groups that finishes first by a measured
  *                       model, so that a single fit spreads over many waves;
  *                       the value calls split below three units per SIMD.
