@@ -83,20 +83,6 @@ __device__ __forceinline__ LevelRecords level_records(const KernelArgs& a, int64
   return L;
 }
 
-// Touches the item's record lines, one per lane and all in flight at once: the
-// sweeps' first reads would each wait for a line that the constants kernel left
-// in another die's cache.  Split units only: 66 units of 17 layers, one node per
-// lane, 39.1 -> 37.6 us a call.  (The one-form kernels do not take it: 529 -> 595 us at 2000
-// units of 26 layers in FP32.)
-__device__ __forceinline__ void warm_records(const KernelArgs& a, int64_t roff, int N, int lane) {
-  const int n = (N + 2) * (lane < 32 ? kRecDoubles : kExtDoubles);
-  const double* r = lane < 32 ? a.consts + roff * kRecDoubles
-                              : reinterpret_cast<const double*>(a.constsf) + roff * kExtDoubles;
-  const int i = (lane & 31) * 8;
-  const double x = r[i < n ? i : n - 1];
-  asm volatile("" ::"v"(x));
-}
-
 // A medium at one node: kz, the real part x of w = x - i B, 1/|w|.
 struct Medium {
   cd kz;
@@ -471,7 +457,6 @@ __global__ __launch_bounds__(64, F64::min_waves(LMAX, false)) void k_grad_select
   const int w = blockIdx.x;
   SplitInfo sp{0, 1, 64};
   const WuInfo u = SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
-  if (SPLIT) warm_records(a, u.roff, u.N, lane);
   stage_shared(s, lane, a.rule);
   const int K = u.smeared ? kSmearNodes : 1;
 

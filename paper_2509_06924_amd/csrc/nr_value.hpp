@@ -94,18 +94,35 @@ __device__ __forceinline__ double node_value(const MathTables& T, const LevelRec
   return cabs2(Qv * crecip(Pv));
 }
 
+// Touches the item's record lines, one per lane and all in flight at once: the
+// sweep's first reads would each wait for a line that the constants kernel left
+// in another die's cache.  (The gradient kernels do not take it: 1400 split units
+// of 10 layers 153 -> 161 us, 2000 of 26 layers in FP32 529 -> 595.)
+__device__ __forceinline__ void warm_records(const KernelArgs& a, int64_t roff, int N, int lane) {
+  const int n = (N + 2) * (lane < 32 ? kRecDoubles : kExtDoubles);
+  const double* r = lane < 32 ? a.consts + roff * kRecDoubles
+                              : reinterpret_cast<const double*>(a.constsf) + roff * kExtDoubles;
+  const int i = (lane & 31) * 8;
+  const double x = r[i < n ? i : n - 1];
+  asm volatile("" ::"v"(x));
+}
+
 // A unit holds npts points of one item; lane g npts + p evaluates point p on
 // the nodes g, g + G, g + 2G, ... (split_setup; G = 1: 64 points, all nodes),
 // and the point's G lanes add their partial sums.  OP: kOpReflectivity writes
-// R_hat, kOpLoglik one logL partial per unit.
-template <class P, int OP>
+// R_hat, kOpLoglik one logL partial per unit.  WARM: the item's record lines are
+// touched first, for launches of so few waves that each waits for its own: 589
+// units of 12 layers 18.5 -> 16.1 us a call, 528 of 18 layers 23.6 -> 21.8.  Of many
+// waves the others cover the wait, and the code costs more: 4096 items of 10 layers
+// 1040 -> 1092 us.
+template <class P, int OP, bool WARM>
 __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
   __shared__ Shared s;
   const int lane = threadIdx.x;
   const int w = blockIdx.x;
   SplitInfo sp;
   const WuInfo u = split_setup(a, w, lane, sp);
-  if (std::is_same<P, F64>::value && sp.G > 1) warm_records(a, u.roff, u.N, lane);
+  if constexpr (WARM) warm_records(a, u.roff, u.N, lane);
   stage_shared(s, lane, a.rule);
   const int K = u.smeared ? kSmearNodes : 1;
   bool badq = !(u.Q > 0.0);
@@ -168,10 +185,19 @@ __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
 template <class P>
 hipError_t launch_value(int op, const KernelArgs& a, int n_wu, hipStream_t st) {
   if (n_wu <= 0) return hipSuccess;
+  if constexpr (std::is_same<P, F64>::value) {
+    if (n_wu <= 2048) {  // two waves per SIMD
+      if (op == kOpReflectivity)
+        hipLaunchKernelGGL((k_value<P, kOpReflectivity, true>), dim3(n_wu), dim3(64), 0, st, a);
+      else
+        hipLaunchKernelGGL((k_value<P, kOpLoglik, true>), dim3(n_wu), dim3(64), 0, st, a);
+      return hipGetLastError();
+    }
+  }
   if (op == kOpReflectivity)
-    hipLaunchKernelGGL((k_value<P, kOpReflectivity>), dim3(n_wu), dim3(64), 0, st, a);
+    hipLaunchKernelGGL((k_value<P, kOpReflectivity, false>), dim3(n_wu), dim3(64), 0, st, a);
   else
-    hipLaunchKernelGGL((k_value<P, kOpLoglik>), dim3(n_wu), dim3(64), 0, st, a);
+    hipLaunchKernelGGL((k_value<P, kOpLoglik, false>), dim3(n_wu), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
