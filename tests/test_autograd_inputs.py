@@ -54,3 +54,10 @@ def test_batched(setup):
     go = torch.stack([GO, 2.0 * GO, -GO, GO.flip(0)])
     got = torch.autograd.grad(setup.ll, setup.leaves, go, is_grads_batched=True)
     assert not setup.calls and _same(got, setup.want(go))
+
+
+def test_zero_tensor_without_memory(setup):
+    go = torch._efficientzerotensor(N, dtype=torch.float64)
+    assert go.data_ptr() == 0
+    got = torch.autograd.grad(setup.ll, setup.leaves, go)
+    assert not setup.calls and all(torch.count_nonzero(g) == 0 for g in got)
