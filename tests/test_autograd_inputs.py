@@ -61,3 +61,11 @@ def test_zero_tensor_without_memory(setup):
     assert go.data_ptr() == 0
     got = torch.autograd.grad(setup.ll, setup.leaves, go)
     assert not setup.calls and all(torch.count_nonzero(g) == 0 for g in got)
+
+
+def test_negated_view(setup):
+    # what the backward of conj() and imag() hands on: the memory holds -go
+    go = torch._neg_view(GO)
+    assert go.is_neg()
+    got = torch.autograd.grad(setup.ll, setup.leaves, go)
+    assert not setup.calls and _same(got, setup.want(-GO))
