@@ -626,11 +626,14 @@ def _plain(problem, g_rows, g_inst, grad_out):
     """Whether nr_scale_gradient may take these tensors as they are: arrays in
     memory of the plan's shapes.  Batched and other wrapped tensors (a backward
     under vmap, is_grads_batched) have the type and the shape, but no storage; autograd's zero tensors have a storage
-    without memory, and a negated view's memory holds the values' negatives."""
+    without memory, and a negated view's memory holds the values' negatives.
+    A forward-mode tangent rides beside the memory and would be lost."""
     import torch
+    import torch.autograd.forward_ad as forward_ad
     return (problem.plan.handle is not None
             and all(type(t) is torch.Tensor and torch._C._has_storage(t)
                     and not t._is_zerotensor() and not t.is_neg() and t.dtype == torch.float64
+                    and forward_ad.unpack_dual(t).tangent is None
                     and t.device == problem.device for t in (g_rows, g_inst, grad_out))
             and g_rows.is_contiguous() and g_inst.is_contiguous()
             and g_rows.shape == problem.layers.shape

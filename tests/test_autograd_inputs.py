@@ -69,3 +69,12 @@ def test_negated_view(setup):
     assert go.is_neg()
     got = torch.autograd.grad(setup.ll, setup.leaves, go)
     assert not setup.calls and _same(got, setup.want(-GO))
+
+
+def test_forward_mode_tangent(setup):
+    import torch.autograd.forward_ad as fw
+    t = torch.tensor([1.0, 0.0, -4.0], dtype=torch.float64)
+    with fw.dual_level():
+        got = torch.autograd.grad(setup.ll, setup.leaves, fw.make_dual(GO, t))
+        primal, tangent = zip(*(fw.unpack_dual(g) for g in got))
+    assert not setup.calls and _same(primal, setup.want(GO)) and _same(tangent, setup.want(t))
