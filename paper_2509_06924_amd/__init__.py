@@ -625,9 +625,10 @@ def tie_map_to_csr(tie_of_entry, n_out):
 def _plain(problem, g_rows, g_inst, grad_out):
     """Whether nr_scale_gradient may take these tensors as they are: arrays in
     memory of the plan's shapes.  Batched and other wrapped tensors (a backward
-    under vmap, is_grads_batched) have the type and the shape, but no storage; autograd's zero tensors have a storage
-    without memory, and a negated view's memory holds the values' negatives.
-    A forward-mode tangent rides beside the memory and would be lost."""
+    under vmap, is_grads_batched) have the type and the shape, but no storage;
+    autograd's zero tensors have a storage without memory, and a negated view's
+    memory holds the values' negatives.  A forward-mode tangent rides beside the
+    memory and would be lost."""
     import torch
     import torch.autograd.forward_ad as forward_ad
     return (problem.plan.handle is not None
@@ -652,7 +653,9 @@ def _scale_gradient(problem, g_rows, g_inst, grad_out):
     _n.check(_n.lib().nr_scale_gradient(problem.plan.handle, _dp(g_rows), _dp(g_inst),
                                         _dp(grad_out), stride, _dp(out), _dp(inst),
                                         _stream(None)))
-    return out, inst[0], inst[1]
+    # (.data: a version counter each, so that in-place work on one does not spoil
+    # a graph that saved the other)
+    return out, inst.data[0], inst.data[1]
 
 
 def _make_autograd():

@@ -78,3 +78,20 @@ def test_forward_mode_tangent(setup):
         got = torch.autograd.grad(setup.ll, setup.leaves, fw.make_dual(GO, t))
         primal, tangent = zip(*(fw.unpack_dual(g) for g in got))
     assert not setup.calls and _same(primal, setup.want(GO)) and _same(tangent, setup.want(t))
+
+
+def test_gradients_are_modified_one_by_one(monkeypatch):
+    """The gradients by scale and bkg come from one launch; in-place work on one
+    leaves graphs that saved the other alone."""
+    monkeypatch.setattr(nr._n, "lib", lambda: SimpleNamespace(nr_scale_gradient=lambda *a: 0))
+    monkeypatch.setattr(nr, "_stream", lambda stream: 0)
+    problem = SimpleNamespace(plan=SimpleNamespace(handle=1, n_items=N),
+                              device=torch.device("cpu"))
+    g = torch.zeros(9, 4, dtype=torch.float64), torch.zeros(N, 2, dtype=torch.float64)
+    _, by_scale, by_bkg = nr._scale_gradient(problem, *g, GO)
+    by_scale.fill_(2.0)
+    w = torch.ones(N, dtype=torch.float64, requires_grad=True)
+    y = (by_scale * w).sum()
+    by_bkg.mul_(3.0)
+    y.backward()
+    assert torch.equal(w.grad, torch.full((N,), 2.0, dtype=torch.float64))
