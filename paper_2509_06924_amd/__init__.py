@@ -628,10 +628,12 @@ def _plain(problem, g_rows, g_inst, grad_out):
     under vmap, is_grads_batched) have the type and the shape, but no storage;
     autograd's zero tensors have a storage without memory, and a negated view's
     memory holds the values' negatives.  A forward-mode tangent rides beside the
-    memory and would be lost."""
+    memory and would be lost, and a dispatch mode (a tracer, an operation
+    counter) would not see the launch."""
     import torch
     import torch.autograd.forward_ad as forward_ad
     return (problem.plan.handle is not None
+            and torch._C._len_torch_dispatch_stack() == 0
             and all(type(t) is torch.Tensor and torch._C._has_storage(t)
                     and not t._is_zerotensor() and not t.is_neg() and t.dtype == torch.float64
                     and forward_ad.unpack_dual(t).tangent is None

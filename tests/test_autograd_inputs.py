@@ -95,3 +95,12 @@ def test_gradients_are_modified_one_by_one(monkeypatch):
     by_bkg.mul_(3.0)
     y.backward()
     assert torch.equal(w.grad, torch.full((N,), 2.0, dtype=torch.float64))
+
+
+def test_traced_backward(setup):
+    """Under a dispatch mode (make_fx, operation counters) the backward consists of
+    operations that the mode sees: a trace's result depends on grad_out."""
+    from torch.fx.experimental.proxy_tensor import make_fx
+    traced = make_fx(lambda go: torch.autograd.grad(setup.ll, setup.leaves, go,
+                                                    retain_graph=True))(GO)
+    assert not setup.calls and _same(traced(-3.0 * GO), setup.want(-3.0 * GO))
