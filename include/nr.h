@@ -281,6 +281,26 @@ nr_status nr_workspace_size(const nr_plan* plan, int32_t op, size_t* bytes);
  * nr_reflectivity output.  Fills host out_off[n_items + 1]. */
 nr_status nr_output_offsets(const nr_plan* plan, int64_t* out_off);
 
+/* The kernel launches of one call in launch order, without the constants and
+ * reduction kernels: what the plan's options and rules came to.  Writes up to
+ * `capacity` entries to out and the number of launches to n_out.  NR_EINVAL for
+ * a NULL plan or n_out, a NULL out with capacity > 0, or an unknown op. */
+typedef struct nr_launch_info {
+  int32_t bucket; /* layer-count bucket (gradient; NR_NUM_BUCKETS: deep stacks), -1: any depth */
+  int32_t form;   /* NR_FORM_*, for gradient calls without a resolution gradient */
+  int32_t mode;   /* NR_MODE_* */
+  int32_t units;  /* work units (waves; deep stacks: one to four waves each) */
+  int32_t stream; /* 0: the caller's, 1 ..: side streams */
+} nr_launch_info;
+#define NR_FORM_RECOMPUTE 0
+#define NR_FORM_STORE 1
+#define NR_FORM_SELECT 3 /* node forms chosen per node (deep stacks: the scan with determinants) */
+#define NR_MODE_FULL 0   /* up to 64 points of one item */
+#define NR_MODE_PACKED 1 /* partial groups of several items */
+#define NR_MODE_SPLIT 2  /* one item's points, the lanes over node groups x points */
+nr_status nr_plan_launches(const nr_plan* plan, int32_t op, int32_t capacity, nr_launch_info* out,
+                           int32_t* n_out);
+
 /* Model curve (Abeles + smearing + instrument, Sec. 2.1 / Sec. 3): writes
  * R_hat for every point of every item into device r_hat[out_off[n_items]],
  * item-major, in the dataset's point order. */

@@ -104,6 +104,17 @@ class Plan:
         _n.check(_n.lib().nr_workspace_size(self._h, op, ctypes.byref(n)))
         return int(n.value)
 
+    def launches(self, op=None):
+        """The launches of one call (default: nr_loglik_grad), as nr_plan_launches
+        lists them, each a dict of bucket, form, mode, units, stream."""
+        op = NR_OP_LOGLIK_GRAD if op is None else op
+        n = ctypes.c_int32()
+        _n.check(_n.lib().nr_plan_launches(self._h, op, 0, None, ctypes.byref(n)))
+        out = (_n.LaunchInfo * max(1, n.value))()
+        _n.check(_n.lib().nr_plan_launches(self._h, op, n.value, ctypes.byref(out),
+                                           ctypes.byref(n)))
+        return [{f: getattr(x, f) for f, _ in x._fields_} for x in out[:n.value]]
+
     def output_offsets(self):
         out = np.zeros(self.n_items + 1, np.int64)
         _n.check(_n.lib().nr_output_offsets(self._h, ctypes.c_void_p(out.ctypes.data)))

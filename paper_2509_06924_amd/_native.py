@@ -32,7 +32,16 @@ EXPORTS = ("nr_version", "nr_status_string", "nr_plan_create", "nr_plan_destroy"
            "nr_loglik_grad_res", "nr_hmc_create", "nr_hmc_destroy", "nr_hmc_init",
            "nr_hmc_transition", "nr_hmc_graph_create", "nr_hmc_adapt", "nr_vi_mvn_create",
            "nr_vi_mvn_destroy", "nr_vi_mvn_step", "nr_vi_mvn_graph_create", "nr_autotune",
-           "nr_smearing_rule", "nr_loglik_grad_noalloc", "nr_scale_gradient")
+           "nr_smearing_rule", "nr_loglik_grad_noalloc", "nr_scale_gradient",
+           "nr_plan_launches")
+
+
+NR_FORM_RECOMPUTE, NR_FORM_STORE, NR_FORM_SELECT = 0, 1, 3
+NR_MODE_FULL, NR_MODE_PACKED, NR_MODE_SPLIT = 0, 1, 2
+
+
+class LaunchInfo(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_int32) for name in ("bucket", "form", "mode", "units", "stream")]
 
 
 class BatchDesc(ctypes.Structure):
@@ -225,6 +234,9 @@ def lib():
         L.nr_tie_sum.argtypes = [ctypes.c_int64, P, P, P, P, P]
         L.nr_scale_gradient.restype = ctypes.c_int32
         L.nr_scale_gradient.argtypes = [P, P, P, P, ctypes.c_int64, P, P, P]
+        L.nr_plan_launches.restype = ctypes.c_int32
+        L.nr_plan_launches.argtypes = [P, ctypes.c_int32, ctypes.c_int32, P,
+                                       ctypes.POINTER(ctypes.c_int32)]
         L.nr_loglik_grad_noalloc.restype = ctypes.c_int32
         L.nr_loglik_grad_noalloc.argtypes = [P, ctypes.POINTER(Values), P, P, P, P]
         L.nr_smearing_rule.restype = ctypes.c_int32

@@ -1681,6 +1681,29 @@ nr_status nr_output_offsets(const nr_plan* p, int64_t* out_off) {
   return NR_OK;
 }
 
+nr_status nr_plan_launches(const nr_plan* p, int32_t op, int32_t capacity, nr_launch_info* out,
+                           int32_t* n_out) {
+  if (!p || !n_out || (capacity > 0 && !out) || op < NR_OP_REFLECTIVITY || op > NR_OP_LOGLIK_GRAD)
+    return NR_EINVAL;
+  static_assert(NR_FORM_RECOMPUTE == kFormRecompute && NR_FORM_STORE == kFormStore &&
+                    NR_FORM_SELECT == kFormSelect && NR_MODE_FULL == kModeFull &&
+                    NR_MODE_PACKED == kModeTail && NR_MODE_SPLIT == kModeSplit,
+                "the header's launch kinds and the kernels' disagree");
+  static_assert(NR_NUM_BUCKETS == kDeepBucket, "the deep stacks' launches follow the buckets");
+  const bool grad = op == NR_OP_LOGLIK_GRAD;
+  const std::vector<Launch>& list = grad ? p->launches_grad : p->launches_fwd;
+  *n_out = (int32_t)list.size();
+  for (int32_t k = 0; k < capacity && k < *n_out; ++k) {
+    const Launch& L = list[k];
+    out[k].bucket = grad ? L.bucket : -1;
+    out[k].form = grad ? L.form : NR_FORM_RECOMPUTE;
+    out[k].mode = L.tail ? kModeTail : L.split ? kModeSplit : kModeFull;
+    out[k].units = L.n_wu;
+    out[k].stream = grad ? L.side : 0;
+  }
+  return NR_OK;
+}
+
 nr_status nr_reflectivity(const nr_plan* p, const nr_values* v, double* r_hat, void* ws,
                           size_t ws_bytes, void* stream) {
   nr_status st = check_call(p, v, false);
