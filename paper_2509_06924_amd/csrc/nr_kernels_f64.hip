@@ -72,8 +72,8 @@ __device__ __forceinline__ double scaled_const(double ch, double cl, double hi, 
 //   |C_m Re(kz_m kz_m+1)| <= 1.01 |C_m| (kz0^2 - min A) <= 1e7  exp_issue_bounded
 // A NaN or an infinity in the rows fails a comparison and empties the range.
 template <ConstsKind KIND>
-__global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, const double* layers,
-                                                    double* rec, float* recf, int n_items) {
+__device__ __forceinline__ void item_consts(const int64_t* row_off, const double* layers,
+                                            double* rec, float* recf, int n_items) {
   constexpr bool EXT = KIND == kConstsScaled || KIND == kConstsScan;
   const int b = blockIdx.x;
   if (b >= n_items) return;
@@ -174,6 +174,20 @@ __global__ __launch_bounds__(64) void k_item_consts(const int64_t* row_off, cons
     }
   }
 }
+
+// (functions rather than instantiations of a template: those would lie behind
+// the large kernels of this file, away from the reductions that run right
+// before and after them)
+#define NR_CONSTS_KERNEL(NAME, KIND)                                                        \
+  __global__ __launch_bounds__(64) void NAME(const int64_t* row_off, const double* layers,  \
+                                             double* rec, float* recf, int n_items) {       \
+    item_consts<KIND>(row_off, layers, rec, recf, n_items);                                 \
+  }
+NR_CONSTS_KERNEL(k_item_consts, kConstsPlain)
+NR_CONSTS_KERNEL(k_item_consts_float, kConstsFloat)
+NR_CONSTS_KERNEL(k_item_consts_scaled, kConstsScaled)
+NR_CONSTS_KERNEL(k_item_consts_scan, kConstsScan)
+#undef NR_CONSTS_KERNEL
 
 // ---------------------------------------------------------------------------
 // Deterministic per-item reductions of the WU records.
@@ -303,10 +317,10 @@ __global__ __launch_bounds__(1024) void k_reduce_grad(ReduceArgs a) {
 hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const double* layers,
                               double* rec, float* recf, int n_items, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  const auto k = kind == kConstsFloat    ? k_item_consts<kConstsFloat>
-                 : kind == kConstsScaled ? k_item_consts<kConstsScaled>
-                 : kind == kConstsScan   ? k_item_consts<kConstsScan>
-                                         : k_item_consts<kConstsPlain>;
+  const auto k = kind == kConstsFloat    ? k_item_consts_float
+                 : kind == kConstsScaled ? k_item_consts_scaled
+                 : kind == kConstsScan   ? k_item_consts_scan
+                                         : k_item_consts;
   hipLaunchKernelGGL(k, dim3(n_items), dim3(64), 0, st, row_off, layers, rec, recf, n_items);
   return hipGetLastError();
 }
