@@ -287,7 +287,8 @@ nr_status nr_output_offsets(const nr_plan* plan, int64_t* out_off);
  * a NULL plan or n_out, a NULL out with capacity > 0, or an unknown op. */
 typedef struct nr_launch_info {
   int32_t bucket; /* layer-count bucket (gradient; NR_NUM_BUCKETS: deep stacks), -1: any depth */
-  int32_t form;   /* NR_FORM_*, for gradient calls without a resolution gradient */
+  int32_t form;   /* NR_FORM_*, for gradient calls without a resolution gradient; value
+                   * calls: NR_FORM_SELECT with node forms, else NR_FORM_RECOMPUTE */
   int32_t mode;   /* NR_MODE_* */
   int32_t units;  /* work units (waves; deep stacks: one to four waves each) */
   int32_t stream; /* 0: the caller's, 1 ..: side streams */

@@ -264,6 +264,7 @@ struct nr_plan {
   int bucket_form[kNumBuckets];  // GradForm of the plain gradient
   bool grad_scaled = false;      // a gradient launch takes the select form
   bool scan_select = false;      // the deep items' launches do
+  bool value_forms = false;      // the value kernels take both node forms (FP64)
   std::vector<int64_t> q_off, row_off, out_off;
   std::vector<int32_t> dataset_of_item;
   std::vector<double> dqq;
@@ -476,11 +477,11 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st,
 nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, bool events,
                        bool res) {
   {
-    // the value kernels and the select form read the scaled factors
+    // the select form and the value kernels with node forms read the scaled factors
     const bool grad_scaled = op == kOpLoglikGrad && p->grad_scaled && !res;
     hipError_t e = launch_item_consts(
         p->precision == NR_F32   ? kConstsFloat
-        : op != kOpLoglikGrad    ? kConstsScaled
+        : op != kOpLoglikGrad    ? (p->value_forms ? kConstsScaled : kConstsPlain)
         : !grad_scaled           ? kConstsPlain
         : p->scan_select         ? kConstsScan
                                  : kConstsScaled,
@@ -541,7 +542,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
                                          : kModeFull;
     const hipStream_t ls = (fork && L.side > 0) ? fj->st[L.side - 1] : st;
     if (!grad)
-      launch_err = launch_forward(p->precision, op, a, L.n_wu, ls);
+      launch_err = launch_forward(p->precision, op, L.split, p->value_forms, a, L.n_wu, ls);
     else if (L.bucket == kDeepBucket)
       launch_err = form == kFormSelect ? launch_grad_scan_select(L.scan_ch, a, L.n_wu, ls)
                                        : launch_grad_scan(res, L.scan_ch, a, L.n_wu, ls);
@@ -999,11 +1000,14 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
     // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
     // 113 / 92 / 98 / 102; 2688: 147 / 130 / 137 / 139; 3584: 152 / 160 / 174 /
-    // 178.  G = 4 leaves nodes over and is never the best; G = 17 is as long as
-    // its waves find a SIMD each: 38 units of 12 layers 20.9 us at 9, 16.4 at 17.
+    // 178.  G = 4 leaves nodes over and is never the best.  G = 17 (one node per
+    // lane) is the best up to 64 units of 64 points in FP64 (64 units at G = 9 /
+    // 17: 12 layers 19.1 / 18.6, 20 layers 24.2 / 22.4, 40 layers 36.3 / 32.0; 96:
+    // 19.6 / 22.5, 24.2 / 27.0, 36.7 / 41.5) and 100 in FP32 (96 units: 17.5 / 18.0,
+    // 21.9 / 21.6, 33.9 / 31.8; 140: 19.7 / 20.4, 25.7 / 25.1, 41.8 / 38.3).
     if (units_fwd > 0)
-      small_G_fwd = 24 * units_fwd <= simds     ? 17
-                    : 4 * units_fwd < simds     ? 9
+      small_G_fwd = (p->precision == NR_F32 ? 10 : 16) * units_fwd <= simds ? 17
+                    : (p->precision == NR_F32 ? 2 : 4) * units_fwd < simds ? 9
                     : 2 * units_fwd < 3 * simds ? 6
                     : units_fwd < 3 * simds     ? 2
                                                 : 1;
@@ -1300,7 +1304,21 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   {
     // the value kernels take any depth: one launch
     std::vector<std::vector<Wu>> all{std::move(fwd_units)};
-    make_full(kOpLoglik, all, p->launches_fwd, true);
+    bool split = false;
+    for (const Wu& u : all[0]) split |= (u.split >> 16) > 1;
+    // The node forms save per level and node and their constants cost per item, so
+    // items of little work in a launch of many waves take the one form.  us a call,
+    // two forms / one, by points x levels of an unsmeared item: 3783 items of 182
+    // 19.9 / 17.1, 546 27.6 / 25.8, 819 33.7 / 32.9, 1183 42.0 / 41.8, 4000 of 800
+    // 38.3 / 33.9; 3094 86.3 / 92; in two waves per SIMD or fewer (whose kernel warms
+    // the records) 1000 of 832 14.8 / 15.8.
+    int64_t steps = 0;
+    for (int b = 0; b < nI; ++b)
+      steps += (p->out_off[b + 1] - p->out_off[b]) * (p->row_off[b + 1] - p->row_off[b] - 1) *
+               (p->dqq[p->dataset_of_item[b]] > 0.0 ? kSmearNodes : 1);
+    p->value_forms = p->precision == NR_F64 &&
+                     (split || (int64_t)all[0].size() <= 2 * simds || steps >= 1300 * (int64_t)nI);
+    make_full(kOpLoglik, all, p->launches_fwd, split);
   }
   make_full(kOpLoglikGrad, grad_units, p->launches_grad, false);
   make_full(kOpLoglikGrad, split_units, p->launches_grad, true);
@@ -1726,7 +1744,7 @@ nr_status nr_plan_launches(const nr_plan* p, int32_t op, int32_t capacity, nr_la
   for (int32_t k = 0; k < capacity && k < *n_out; ++k) {
     const Launch& L = list[k];
     out[k].bucket = grad ? L.bucket : -1;
-    out[k].form = grad ? L.form : NR_FORM_RECOMPUTE;
+    out[k].form = grad ? L.form : p->value_forms ? NR_FORM_SELECT : NR_FORM_RECOMPUTE;
     out[k].mode = L.tail ? kModeTail : L.split ? kModeSplit : kModeFull;
     out[k].units = L.n_wu;
     out[k].stream = grad ? L.side : 0;

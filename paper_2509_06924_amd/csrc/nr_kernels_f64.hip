@@ -325,9 +325,10 @@ hipError_t launch_item_consts(ConstsKind kind, const int64_t* row_off, const dou
   return hipGetLastError();
 }
 
-hipError_t launch_forward(int precision, int op, const KernelArgs& a, int n_wu, hipStream_t st) {
-  return precision == NR_F32 ? launch_forward_f32(op, a, n_wu, st)
-                             : launch_value<F64>(op, a, n_wu, st);
+hipError_t launch_forward(int precision, int op, bool split, bool forms, const KernelArgs& a,
+                          int n_wu, hipStream_t st) {
+  return precision == NR_F32 ? launch_forward_f32(op, split, a, n_wu, st)
+                             : launch_value<F64>(op, split, forms, a, n_wu, st);
 }
 
 hipError_t launch_grad(int precision, int bucket, int form, int mode, const KernelArgs& a,

@@ -110,31 +110,41 @@ __device__ __forceinline__ void warm_records(const KernelArgs& a, int64_t roff, 
 // A unit holds npts points of one item; lane g npts + p evaluates point p on
 // the nodes g, g + G, g + 2G, ... (split_setup; G = 1: 64 points, all nodes),
 // and the point's G lanes add their partial sums.  OP: kOpReflectivity writes
-// R_hat, kOpLoglik one logL partial per unit.  WARM: the item's record lines are
-// touched first, for launches of so few waves that each waits for its own: 589
-// units of 12 layers 18.5 -> 16.1 us a call, 528 of 18 layers 23.6 -> 21.8.  Of many
-// waves the others cover the wait, and the code costs more: 4096 items of 10 layers
-// 1040 -> 1092 us.
-template <class P, int OP, bool WARM>
+// R_hat, kOpLoglik one logL partial per unit.
+// FEW: launches of so few waves that each waits for its own record loads.  FP64,
+// up to two waves per SIMD: the item's record lines are touched first (589 units
+// of 12 layers 18.5 -> 16.1 us a call, 528 of 18 layers 23.6 -> 21.8).  FP32, up to
+// one: nodes counted per lane, whose record loads are vector loads and run ahead
+// (45 units of 64 points in 17 groups, 20 layers 20.1 -> 18.2 us, 40 layers 28.5 ->
+// 26.0).  Of many waves the others cover the wait, and either costs more: 4096
+// items of 10 layers FP64 1040 -> 1092 us, 64 units of 20 layers in 17 groups FP32
+// 20.1 -> 20.4, 700 in 9 groups 52.8 -> 56.5.
+// SPLIT: whether any unit of the launch has node groups.  Without, the divisions
+// of split_setup go and the counter is uniform anyway (28000 units of one node and
+// one layer FP64 41.7 -> 38.0 us a call).
+// FORMS (FP64): the node forms of nr_select.hpp, or the one form on plain records
+// (28000 units of one node and one layer 38.3 -> 33.9 us a call; the rule in
+// nr_plan_create_ex).
+template <class P, int OP, bool SPLIT, bool FEW, bool FORMS>
 __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
   __shared__ Shared s;
   const int lane = threadIdx.x;
   const int w = blockIdx.x;
-  SplitInfo sp;
-  const WuInfo u = split_setup(a, w, lane, sp);
-  if constexpr (WARM) warm_records(a, u.roff, u.N, lane);
+  SplitInfo sp{0, 1, 64};
+  const WuInfo u = SPLIT ? split_setup(a, w, lane, sp) : wu_setup(a, w, lane);
+  if constexpr (FEW && FORMS) warm_records(a, u.roff, u.N, lane);
   stage_shared(s, lane, a.rule);
   const int K = u.smeared ? kSmearNodes : 1;
   bool badq = !(u.Q > 0.0);
   double Rsm = 0.0;
   for (int k0 = 0; k0 < K; k0 += sp.G) {
     const int k = k0 + sp.g;
-    if (!(u.active && k < K)) continue;
+    if (SPLIT && !(u.active && k < K)) continue;
     const double q = (K == 1) ? u.Q : smear_at(u.Q, u.sig, ld(s.t[k]));
     badq |= !(q > 0.0);
     const double wk = (K == 1) ? 1.0 : ld(s.w[k]);
     double R;
-    if constexpr (std::is_same<P, F64>::value) {
+    if constexpr (FORMS) {
       // (the counter is the wave's: the records stay scalar loads)
       const LevelRecords L = level_records(a, u.roff, u.N, k0);
       const double kz0sq = kz0_squared(q);
@@ -142,11 +152,12 @@ __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
       R = __ballot(out) == 0 ? node_value<true>(s.tab, L, u.N, q)
                              : node_value<false>(s.tab, L, u.N, q);
     } else {
-      R = node_reflectivity(s.tab, item_layers<P>(a, u.roff, u.N, k0), u.N, q);
+      R = node_reflectivity(s.tab, item_layers<P>(a, u.roff, u.N, SPLIT && FEW ? k : k0), u.N,
+                            q);
     }
     Rsm += wk * R;
   }
-  if (sp.G > 1) {
+  if (SPLIT && sp.G > 1) {
     double tot = 0.0;
     int bq = 0;
     for (int gg = 0; gg < sp.G; ++gg) {
@@ -182,22 +193,32 @@ __global__ __launch_bounds__(64) void k_value(KernelArgs a) {
   }
 }
 
-template <class P>
-hipError_t launch_value(int op, const KernelArgs& a, int n_wu, hipStream_t st) {
-  if (n_wu <= 0) return hipSuccess;
-  if constexpr (std::is_same<P, F64>::value) {
-    if (n_wu <= 2048) {  // two waves per SIMD
-      if (op == kOpReflectivity)
-        hipLaunchKernelGGL((k_value<P, kOpReflectivity, true>), dim3(n_wu), dim3(64), 0, st, a);
-      else
-        hipLaunchKernelGGL((k_value<P, kOpLoglik, true>), dim3(n_wu), dim3(64), 0, st, a);
-      return hipGetLastError();
-    }
-  }
-  if (op == kOpReflectivity)
-    hipLaunchKernelGGL((k_value<P, kOpReflectivity, false>), dim3(n_wu), dim3(64), 0, st, a);
+template <class P, int OP>
+static void launch_value_op(bool split, bool few, bool forms, const KernelArgs& a, int n_wu,
+                            hipStream_t st) {
+  constexpr bool kF64 = std::is_same<P, F64>::value;
+  if (kF64 && !forms)
+    hipLaunchKernelGGL((k_value<P, OP, false, false, false>), dim3(n_wu), dim3(64), 0, st, a);
+  else if (split && few)
+    hipLaunchKernelGGL((k_value<P, OP, true, true, kF64>), dim3(n_wu), dim3(64), 0, st, a);
+  else if (split)
+    hipLaunchKernelGGL((k_value<P, OP, true, false, kF64>), dim3(n_wu), dim3(64), 0, st, a);
+  else if (kF64 && few)
+    hipLaunchKernelGGL((k_value<P, OP, false, kF64, kF64>), dim3(n_wu), dim3(64), 0, st, a);
   else
-    hipLaunchKernelGGL((k_value<P, kOpLoglik, false>), dim3(n_wu), dim3(64), 0, st, a);
+    hipLaunchKernelGGL((k_value<P, OP, false, false, kF64>), dim3(n_wu), dim3(64), 0, st, a);
+}
+
+// (forms: FP64, the scaled constants were made; without them no unit is split)
+template <class P>
+hipError_t launch_value(int op, bool split, bool forms, const KernelArgs& a, int n_wu,
+                        hipStream_t st) {
+  if (n_wu <= 0) return hipSuccess;
+  const bool few = n_wu <= (std::is_same<P, F64>::value ? 2048 : 1024);
+  if (op == kOpReflectivity)
+    launch_value_op<P, kOpReflectivity>(split, few, forms, a, n_wu, st);
+  else
+    launch_value_op<P, kOpLoglik>(split, few, forms, a, n_wu, st);
   return hipGetLastError();
 }
 

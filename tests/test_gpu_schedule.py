@@ -1,0 +1,70 @@
+"""What the rules of a plan's schedule come to, by the launch list: each line was
+measured, and a change that moves it shows here instead of as a slower call."""
+import numpy as np
+import pytest
+
+from nr_check import check_R, check_logL, logL_bound
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nr():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines are those of 1024 SIMDs")
+    import paper_2509_06924_amd as nr
+    return nr
+
+
+def _batch(L, nq, items, dqq=0.05):
+    from paper_2509_06924_amd import inputs
+    rng = np.random.default_rng(1)
+    Q = inputs.log_grid(0.008, 0.3, nq)
+    Ls = L if isinstance(L, (list, tuple)) else [L] * items
+    return inputs._pack("schedule", [(Q, *inputs.synthetic_curve(Q, rng), dqq)],
+                        [(0, inputs.draw_stack(rng, k), 0.97, 1.3e-7) for k in Ls], {})
+
+
+# value units of 64 points: node groups per point, and waves of 3 points at 17 groups
+@pytest.mark.parametrize("precision,items,groups", [
+    ("f64", 64, 17), ("f64", 65, 9), ("f64", 256, 6), ("f32", 102, 17), ("f32", 511, 9),
+    ("f32", 512, 6)])
+def test_value_groups_of_small_plans(nr, precision, items, groups):
+    p = nr.Problem.from_batch(_batch(5, 64, items),
+                              precision=nr.NR_F32 if precision == "f32" else nr.NR_F64)
+    (launch,) = p.plan.launches(nr.NR_OP_LOGLIK)
+    points = 64 // groups
+    assert launch["units"] == items * -(-64 // points)
+
+
+@pytest.mark.parametrize("items", [46, 47])  # 1012 and 1034 waves
+def test_fp32_value_kernels_about_one_wave_per_simd(nr, orc, items):
+    batch = _batch(20, 64, items)
+    p = nr.Problem.from_batch(batch, precision=nr.NR_F32)
+    R = p.reflectivity().cpu().numpy().reshape(items, 64)
+    for b in (0, items - 1):
+        Q, *_, d = batch.data_of(b)
+        # (the FP32 variant's bound, tests/test_gpu_fp32.py)
+        check_R(R[b], orc.model_curve(batch.rows_of(b), 0.97, 1.3e-7, Q, d), tol=1e-4)
+
+
+# unsmeared, waves and points x levels of an item about the lines of the one form
+@pytest.mark.parametrize("L,nq,items,forms", [
+    (1, 64, 2048, True), (1, 64, 2049, False), (7, 162, 700, False), (7, 163, 700, True)])
+def test_value_form_of_items_of_little_work(nr, orc, L, nq, items, forms):
+    batch = _batch(L, nq, items, dqq=0.0)
+    p = nr.Problem.from_batch(batch)
+    (launch,) = p.plan.launches(nr.NR_OP_REFLECTIVITY)
+    assert launch["form"] == (nr._n.NR_FORM_SELECT if forms else nr._n.NR_FORM_RECOMPUTE)
+    R = p.reflectivity().cpu().numpy().reshape(items, nq)
+    ll = p.loglik().cpu().numpy()
+    assert int(p.item_status.abs().sum().item()) == 0
+    for b in (0, 1, items - 1):
+        Q, Robs, e, d = batch.data_of(b)
+        Ro = orc.model_curve(batch.rows_of(b), 0.97, 1.3e-7, Q, d)
+        check_R(R[b], Ro)
+        llo = orc.loglik(batch.rows_of(b), 0.97, 1.3e-7, Q, Robs, e, d)
+        check_logL(ll[b], llo, logL_bound(Ro, Robs, e))
