@@ -119,7 +119,7 @@ struct Launch {
   int form = kFormRecompute;  // gradient: the kernel form (resolution calls take their own)
   bool tail = false;
   bool split = false;  // split tail units (one item's partial group, lanes over node groups)
-  bool one = false;    // split units of one node per lane, for the per-lane node counter
+  bool one[2] = {};    // split units whose one node is counted per lane: plain, resolution
   int scan_ch = 0;     // deep lists: the largest levels-per-lane of its items at 64 lanes
   int side = 0;        // 0: the caller's stream, k: the plan's side stream k - 1
   double est = 0.0;    // gradient: estimated time (see launch_estimate)
@@ -405,6 +405,22 @@ double launch_estimate(int precision, int lmax, int64_t waves, int nodes, int64_
   return f * (nodes + e) * (lmax + 1) * (one_wave ? 1.26 : 1.0);
 }
 
+// Whether a gradient launch of one node per lane counts it per lane.  A wave alone
+// on its SIMD that runs one node waits for each scalar load of a record it has
+// not read yet; the vector loads of a per-lane counter run ahead.  Up to a
+// quarter of the SIMDs busy that is the faster one at every depth (us a call per
+// wave / per lane, one item of 200 points: 16 layers FP32 30.0 / 27.7, 20 layers 35.7
+// / 32.6, 40 layers with resolution 61.5 / 57.4, FP64 79.6 / 77.0; FP32 at 6 layers
+// 20.6 / 21.0).  With more waves the scalar loads win in resolution calls (10 items of
+// 184 points, 40 layers FP64 93 / 112) and at 14 and 18 layers in FP32 (1.5-3 %), the
+// vector loads in the rest: 45 items of 48 points, 16 layers FP32 29.6 / 27.5, 20
+// layers 36.8 / 35.5.
+bool lane_counter_pays(int precision, int lmax, bool res, int64_t waves, int64_t simds) {
+  const bool few = 4 * waves <= simds;
+  if (precision == NR_F64) return few || (lmax >= 24 && !res);
+  return (few && lmax != 6) || (lmax >= 16 && lmax != 18 && (!res || lmax <= 28));
+}
+
 // Node groups per point for the gradient of a small plan: the G whose launches
 // (one per depth bucket, on up to 1 + kSideStreams streams) take the least
 // estimated time.  Units of 400 points, 10 layers, us a call at G = 1 / 2 / 3 /
@@ -537,7 +553,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     a.tail_rec = L.lane_rec;
     const int form = res ? kFormRecomputeRes : L.form;
     const int mode = L.tail              ? kModeTail
-                     : L.one && !res     ? kModeSplitOne
+                     : L.one[res]        ? kModeSplitOne
                      : L.split           ? kModeSplit
                                          : kModeFull;
     const hipStream_t ls = (fork && L.side > 0) ? fj->st[L.side - 1] : st;
@@ -986,12 +1002,13 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   simds = std::max<int64_t>(simds, 1);
   int small_G = 1, small_G_fwd = 1;
   if (p->opts.split_tails & NR_SPLIT_SMALL) {
-    int64_t units = 0, units_fwd = 0;
+    int64_t units = 0, units_fwd = 0, levels_fwd = 0;
     for (int b = 0; b < nI; ++b) {
       const int s = p->dataset_of_item[b];
       const int N = (int)(p->row_off[b + 1] - p->row_off[b]) - 2;
       const int64_t u = (p->q_off[s + 1] - p->q_off[s] + kWuPoints - 1) / kWuPoints;
       units_fwd += u;
+      levels_fwd += u * (N + 1);
       if (bucket_of(N) != kDeepBucket) units += u;
     }
     if (units > 0 && units < kSmallPlanWaves * simds)
@@ -1004,10 +1021,15 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     // lane) is the best up to 64 units of 64 points in FP64 (64 units at G = 9 /
     // 17: 12 layers 19.1 / 18.6, 20 layers 24.2 / 22.4, 40 layers 36.3 / 32.0; 96:
     // 19.6 / 22.5, 24.2 / 27.0, 36.7 / 41.5) and 100 in FP32 (96 units: 17.5 / 18.0,
-    // 21.9 / 21.6, 33.9 / 31.8; 140: 19.7 / 20.4, 25.7 / 25.1, 41.8 / 38.3).
+    // 21.9 / 21.6, 33.9 / 31.8; 140: 19.7 / 20.4, 25.7 / 25.1, 41.8 / 38.3).  Deep FP32
+    // items keep G = 9 longer (339 units at G = 6 / 9: 6 layers 17.7 / 18.2, 16 layers
+    // 30.1 / 27.9, 28 layers 44.6 / 39.8, 40 layers 59.2 / 51.4; 312: 4 layers 17.6 / 19.4,
+    // 12 layers 26.9 / 27.1).
+    const bool f32 = p->precision == NR_F32;
+    const bool f32_deep = f32 && levels_fwd >= 14 * units_fwd;
     if (units_fwd > 0)
-      small_G_fwd = (p->precision == NR_F32 ? 10 : 16) * units_fwd <= simds ? 17
-                    : (p->precision == NR_F32 ? 2 : 4) * units_fwd < simds ? 9
+      small_G_fwd = (f32 ? 10 : 16) * units_fwd <= simds        ? 17
+                    : (f32_deep ? 2 : 4) * units_fwd < simds ? 9
                     : 2 * units_fwd < 3 * simds ? 6
                     : units_fwd < 3 * simds     ? 2
                                                 : 1;
@@ -1288,8 +1310,10 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         const int G = std::max(1, u.split >> 16);
         nodes = std::max(nodes, (K + G - 1) / G);
       }
-      L.one = split && nodes == 1 && L.form == kFormRecompute && L.bucket != kDeepBucket &&
-              kBucketLmax[L.bucket] >= kOneNodeLayers;
+      for (bool res : {false, true})
+        L.one[res] = op == kOpLoglikGrad && split && nodes == 1 && L.bucket != kDeepBucket &&
+                     (res || L.form != kFormSelect) &&
+                     lane_counter_pays(p->precision, kBucketLmax[L.bucket], res, L.n_wu, simds);
       L.est = L.bucket == kDeepBucket
                   ? 1.5 * 8 * nodes * L.n_wu * std::max(1, L.scan_ch / 8) / (double)simds
                   : launch_estimate(p->precision, kBucketLmax[L.bucket], L.n_wu, nodes, simds);

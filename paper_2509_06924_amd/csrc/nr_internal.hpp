@@ -43,8 +43,6 @@ constexpr int kOpLoglikGrad = NR_OP_LOGLIK_GRAD;
 #define NR_BUCKETS(X) NR_BUCKETS_SHALLOW(X) NR_BUCKETS_DEEP(X)
 constexpr int kFirstDeepBucket = 7;
 constexpr int kBucketLmax[] = {1, 2, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40};
-// from this depth on, split units of one node per lane count nodes per lane (see PerLane)
-constexpr int kOneNodeLayers = 24;
 constexpr int kNumBuckets = sizeof(kBucketLmax) / sizeof(int);
 static_assert(kNumBuckets == NR_NUM_BUCKETS, "bucket table and ABI disagree");
 
@@ -136,7 +134,8 @@ hipError_t launch_forward(int precision, int op, bool split, bool forms, const K
 enum GradForm { kFormRecompute = 0, kFormStore = 1, kFormRecomputeRes = 2, kFormSelect = 3 };
 // mode: kModeFull (64 points of one item), kModeTail (packed partial
 // groups of several items), kModeSplit (one item's partial group, lanes over
-// node groups x points), kModeSplitOne (split units of one node per lane)
+// node groups x points), kModeSplitOne (split units
+// of one node per lane that count it per lane)
 enum WuMode { kModeFull = 0, kModeTail = 1, kModeSplit = 2, kModeSplitOne = 3 };
 hipError_t launch_grad(int precision, int bucket, int form, int mode, const KernelArgs& a,
                        int n_wu, hipStream_t st);

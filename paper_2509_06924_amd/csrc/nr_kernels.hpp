@@ -1123,16 +1123,30 @@ __device__ __forceinline__ void write_grad_record(const KernelArgs& a, const WuI
 //   [3 + 3NR + m]  sum Re(conj(ubar) kz_{m-1} kz_m)   (sigma_m factor applied later)
 //   [3 + 4NR]      d/d(dQ/Q) (relative resolution)
 // ---------------------------------------------------------------------------
-// The precision with nodes counted per lane in split units.  A wave alone on
-// its SIMD that runs one node waits for each scalar load of a record it has
-// not read yet; the per-lane counter's vector loads run ahead.  One item of 200
-// points, 26 layers FP32: 50.3 -> 43.4 us a call; 7 items of 178 points, 38
-// layers FP64: 80.1 -> 71.3 us.  With more waves or nodes the scalar loads are the
-// faster ones (500 items, 26 layers FP32: 678 us per lane, 529 per wave).
+// In a split unit the node counter differs between lanes, and the layer records,
+// indexed with it (zero_mask), become vector loads; counted per wave they stay
+// scalar loads.  The buckets whose split kernels count per wave:
+// the 6-20-layer FP64 forms (beside k_grad_select: by explicit option, or at one
+// node per lane), the 1-2-layer FP64 and the 8-12-layer FP32 ones keep the per-lane
+// counter, and so do the FP32 resolution forms up to 6 layers (us a call per wave /
+// per lane: 10 items of 180 points, 10 layers FP32 26.9 / 24.8; 39 items of 480
+// points, 2 layers FP64 22.9 / 22.3; resolution, 150 items of 300 points, 6 layers
+// FP32 57.0 / 54.4; but 1000 items of 84 points, 4 layers FP64 70 / 89, 20 layers
+// FP32 per lane 1.4 times as long).
+template <class P>
+constexpr bool wave_counter(int lmax, bool res) {
+  return std::is_same<typename P::real, double>::value
+             ? (lmax > 2 && lmax < kSelectMinLayers) || lmax > kSelectMaxLayers
+             : (lmax < 8 && !(res && lmax <= 6)) || lmax > 12;
+}
+// The precision with nodes counted per lane in the other buckets too
+// (kModeSplitOne; the rule and its measurements at lane_counter_pays).
 template <class P>
 struct PerLane : P {
   static constexpr bool kLaneCounter = true;
 };
+template <class P, int LMAX, bool RES>
+using LanePrecision = typename std::conditional<wave_counter<P>(LMAX, RES), PerLane<P>, P>::type;
 
 template <class P, int LMAX, bool STORE, bool TAIL, bool RES, bool SPLIT = false>
 __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void k_loglik_grad(
@@ -1173,16 +1187,7 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
   // a split unit's lane takes every G-th node from its group's first
   const int k0 = SPLIT ? (u.active ? sp.g : K) : 0;
   const int kstep = SPLIT ? sp.G : 1;
-  // In a split unit the counter differs between lanes, and the layer records,
-  // indexed with it (zero_mask), become vector loads; kWaveCounter counts per
-  // wave instead.  The 6-20-layer FP64 forms (beside k_grad_select: by explicit
-  // option, or at one node per lane) and the 8-12-layer FP32 ones keep the
-  // per-lane counter: 10 items of 180 points, 10 layers FP32 26.9 us a call per
-  // wave, 24.8 per lane; 40 items of 300 points, 41.5 / 38.8; at 6 layers 26.1 / 27.3.
-  constexpr bool kWaveCounter =
-      SPLIT && !P::kLaneCounter &&
-      (std::is_same<P, F64>::value ? LMAX < kSelectMinLayers || LMAX > kSelectMaxLayers
-                                   : LMAX < 8 || LMAX > 12);
+  constexpr bool kWaveCounter = SPLIT && !P::kLaneCounter && wave_counter<P>(LMAX, RES);
   for (int kk = kWaveCounter ? 0 : k0; kk < K; kk += kstep) {
     const int k = kWaveCounter ? kk + k0 : kk;
     if (kWaveCounter && k >= K) continue;
@@ -1229,6 +1234,9 @@ __global__ __launch_bounds__(64, P::min_waves(LMAX, STORE, TAIL || SPLIT)) void 
 #define NR_LAUNCH(LM, S, RES)                                                                 \
   if (mode == kModeTail)                                                                      \
     hipLaunchKernelGGL((k_loglik_grad<P, LM, S, true, RES>), dim3(n_wu), dim3(64), 0, st, a);  \
+  else if (mode == kModeSplitOne)                                                             \
+    hipLaunchKernelGGL((k_loglik_grad<LanePrecision<P, LM, RES>, LM, S, false, RES, true>),   \
+                       dim3(n_wu), dim3(64), 0, st, a);                                       \
   else if (mode == kModeSplit)                                                                \
     hipLaunchKernelGGL((k_loglik_grad<P, LM, S, false, RES, true>), dim3(n_wu), dim3(64), 0,  \
                        st, a);                                                                \

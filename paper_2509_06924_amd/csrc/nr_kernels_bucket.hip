@@ -27,15 +27,6 @@ hipError_t NR_DEEP_LAUNCHER(NR_PREC, NR_BUCKET_LMAX)(int form, int mode, const K
       return hipErrorInvalidValue;
     }
   }
-  if (mode == kModeSplitOne) {
-    if constexpr (LM >= kOneNodeLayers) {
-      hipLaunchKernelGGL((k_loglik_grad<PerLane<P>, LM, false, false, false, true>), dim3(n_wu),
-                         dim3(64), 0, st, a);
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;
-    }
-  }
   NR_FORMS(LM)
   return hipGetLastError();
 }

@@ -29,11 +29,11 @@ def _batch(L, nq, items, dqq=0.05):
 
 
 # value units of 64 points: node groups per point, and waves of 3 points at 17 groups
-@pytest.mark.parametrize("precision,items,groups", [
-    ("f64", 64, 17), ("f64", 65, 9), ("f64", 256, 6), ("f32", 102, 17), ("f32", 511, 9),
-    ("f32", 512, 6)])
-def test_value_groups_of_small_plans(nr, precision, items, groups):
-    p = nr.Problem.from_batch(_batch(5, 64, items),
+@pytest.mark.parametrize("precision,L,items,groups", [
+    ("f64", 5, 64, 17), ("f64", 5, 65, 9), ("f64", 5, 256, 6), ("f32", 5, 102, 17),
+    ("f32", 5, 103, 9), ("f32", 12, 256, 6), ("f32", 13, 511, 9), ("f32", 13, 512, 6)])
+def test_value_groups_of_small_plans(nr, precision, L, items, groups):
+    p = nr.Problem.from_batch(_batch(L, 64, items),
                               precision=nr.NR_F32 if precision == "f32" else nr.NR_F64)
     (launch,) = p.plan.launches(nr.NR_OP_LOGLIK)
     points = 64 // groups
