@@ -255,6 +255,14 @@ bool side_pool_free(const SidePool& pool, hipStream_t st) {
   return true;
 }
 
+// The launches of a gradient call and the records they write.
+struct GradSchedule {
+  std::vector<Launch> launches;
+  RecordLists lists;
+  int64_t records = 0;  // doubles
+  int n_side = 0;       // streams beside the caller's
+};
+
 }  // namespace
 
 struct nr_plan {
@@ -268,24 +276,27 @@ struct nr_plan {
   std::vector<int64_t> q_off, row_off, out_off;
   std::vector<int32_t> dataset_of_item;
   std::vector<double> dqq;
-  int64_t rec_ll_total = 0, rec_grad_total = 0;
+  int64_t rec_ll_total = 0;
   // device copies
   int32_t* d_dataset_of_item = nullptr;
   int64_t* d_q_off = nullptr;
   int64_t* d_row_off = nullptr;
   double* d_dqq = nullptr;
   int64_t* d_out_off = nullptr;
-  RecordLists lists_ll, lists_grad;
+  RecordLists lists_ll;
   double* d_rule = nullptr;
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
-  std::vector<Launch> launches_fwd, launches_grad;
+  std::vector<Launch> launches_fwd;
+  // grad_res: of calls with the resolution derivative, where they have their own
+  GradSchedule grad, grad_res;
+  bool res_own = false;
+  const GradSchedule& schedule(bool res) const { return res && res_own ? grad_res : grad; }
   uint8_t* d_row_kind = nullptr;  // 0 fronting, 1 layer, 2 backing, per row
   int uniform_rows = 0;           // rows per item if all items agree, else 0
   int max_rows = 2;               // rows of the deepest item
   double node_t[kSmearNodes], node_w[kSmearNodes];
   std::vector<void*> owned;
   // streams beside the caller's for the gradient's launches (side_stream)
-  int n_side = 0;
   bool pooled = false;        // holds a use of the device's SidePool
   mutable ForkJoin cap;       // calls under graph capture; made by the first
   mutable std::mutex cap_mu;  // one captured fork ... join sequence at a time
@@ -300,7 +311,6 @@ void plan_free(nr_plan* p) {
   fork_join_free(p->cap);
   if (p->pooled) side_pool_release(p->device);
   p->pooled = false;
-  p->n_side = 0;
 }
 
 nr_status validate_desc(const nr_batch_desc* d) {
@@ -373,7 +383,7 @@ const float* consts_floats(const nr_plan* p, const double* ws) {
 size_t op_doubles(const nr_plan* p, int op) {
   size_t n = consts_doubles(p);
   if (op == NR_OP_LOGLIK) n += (size_t)p->rec_ll_total;
-  if (op == NR_OP_LOGLIK_GRAD) n += (size_t)p->rec_grad_total;
+  if (op == NR_OP_LOGLIK_GRAD) n += (size_t)std::max(p->grad.records, p->grad_res.records);
   return n;
 }
 
@@ -510,9 +520,10 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     if (e != hipSuccess) return hip_fail(e, "timing event");
   }
   const bool grad = (op == kOpLoglikGrad);
+  const GradSchedule& sched = p->schedule(res);
   // fork: the side streams wait for the constants (and everything before
   // them on st); join: st waits for the side streams' launches
-  bool fork = grad && p->n_side > 0;
+  bool fork = grad && sched.n_side > 0;
   std::unique_lock<std::mutex> lock;
   // A call being captured into a graph uses streams and events of its plan, so
   // that none is shared between captured and eager fork/joins.
@@ -526,24 +537,24 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
     if (capturing) {
       fj = &p->cap;
       RelaxedCapture relaxed;
-      e = fork_join_make(p->cap, p->n_side);
+      e = fork_join_make(p->cap, sched.n_side);
     } else if (side_pool_free(pool, st)) {
       fj = &pool.set;
       pool.caller = st;
-      pool.used = p->n_side;
+      pool.used = sched.n_side;
     } else {
       fork = false;
       lock.unlock();
     }
     if (fork) {
       if (e == hipSuccess) e = hipEventRecord(fj->fork, st);
-      for (int k = 0; k < p->n_side && e == hipSuccess; ++k)
+      for (int k = 0; k < sched.n_side && e == hipSuccess; ++k)
         e = hipStreamWaitEvent(fj->st[k], fj->fork, 0);
     }
     if (e != hipSuccess) return hip_fail(e, "side stream fork");
   }
   hipError_t launch_err = hipSuccess;
-  for (const Launch& L : grad ? p->launches_grad : p->launches_fwd) {
+  for (const Launch& L : grad ? sched.launches : p->launches_fwd) {
     a.wu_item = L.item;
     a.wu_p0 = L.p0;
     a.wu_rec = L.rec;
@@ -569,7 +580,7 @@ nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st, b
   if (fork) {
     // joined even after a failed launch, so that a capture stays well formed
     hipError_t e = hipSuccess;
-    for (int k = 0; k < p->n_side; ++k) {
+    for (int k = 0; k < sched.n_side; ++k) {
       hipError_t ek = hipEventRecord(fj->join[k], fj->st[k]);
       if (ek == hipSuccess) ek = hipStreamWaitEvent(st, fj->join[k], 0);
       if (e == hipSuccess) e = ek;
@@ -599,9 +610,10 @@ nr_status enqueue_grad(const nr_plan* p, const nr_values* v, double* logL, doubl
   ReduceArgs r;
   std::memset(&r, 0, sizeof(r));
   r.n_items = p->n_items;
-  r.item_wu_first = p->lists_grad.first;
-  r.item_wu_count = p->lists_grad.count;
-  r.rec_of_wu = p->lists_grad.offs;
+  const RecordLists& lists = p->schedule(g_res != nullptr).lists;
+  r.item_wu_first = lists.first;
+  r.item_wu_count = lists.count;
+  r.rec_of_wu = lists.offs;
   r.rec = a.rec;
   r.row_off = p->d_row_off;
   r.layers = v->layers;
@@ -979,13 +991,10 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   // not run with the idle lanes of the deepest one
   constexpr int kDeepClasses = 3;
   std::vector<Wu> fwd_units;
-  std::vector<std::vector<Wu>> grad_units(kNumBuckets + kDeepClasses);
-  std::vector<std::vector<Wu>> split_units(kNumBuckets);
   int scan_ch[kDeepClasses] = {0, 0, 0};
-  std::map<std::pair<int, int>, std::vector<Tail>> tails;  // (depth, nodes)
-  std::vector<int64_t> ll_first(nI), ll_offs, gr_first(nI), gr_offs;
-  std::vector<int32_t> ll_count(nI), gr_count(nI);
-  int64_t rec_ll = 0, rec_gr = 0;
+  std::vector<int64_t> ll_first(nI), ll_offs;
+  std::vector<int32_t> ll_count(nI);
+  int64_t rec_ll = 0;
   // Small problems (NR_SPLIT_SMALL): one wave per 64 points leaves most of the
   // device idle, or its last round nearly empty, for as long as a wave takes
   // over the 17 nodes of its points; splitting the nodes of every point group
@@ -1000,7 +1009,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       simds = 4 * (int64_t)cus;
   }
   simds = std::max<int64_t>(simds, 1);
-  int small_G = 1, small_G_fwd = 1;
+  int small_G = 1, small_G_fwd = 1, res_G = 1;
   if (p->opts.split_tails & NR_SPLIT_SMALL) {
     int64_t units = 0, units_fwd = 0, levels_fwd = 0;
     for (int b = 0; b < nI; ++b) {
@@ -1013,6 +1022,11 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     }
     if (units > 0 && units < kSmallPlanWaves * simds)
       small_G = pick_node_groups(p, units, simds);
+    // The resolution form's split kernels spend more registers on the derivative and
+    // lose from two units per SIMD on (us a call, split / whole: 1000 items of 84 points, 10
+    // layers FP64 182.9 / 171.7, 2000 of 96, 14 layers 632 / 553, 16 layers FP32 447 / 353):
+    // those calls then have a schedule of their own.
+    res_G = units < 2 * simds ? small_G : 1;
     // Value units, by how many each SIMD would get unsplit.  Measured on MI355X
     // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
     // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
@@ -1028,14 +1042,14 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     const bool f32 = p->precision == NR_F32;
     const bool f32_deep = f32 && levels_fwd >= 14 * units_fwd;
     if (units_fwd > 0)
-      small_G_fwd = (f32 ? 10 : 16) * units_fwd <= simds        ? 17
+      small_G_fwd = (f32 ? 10 : 16) * units_fwd <= simds  ? 17
                     : (f32_deep ? 2 : 4) * units_fwd < simds ? 9
-                    : 2 * units_fwd < 3 * simds ? 6
-                    : units_fwd < 3 * simds     ? 2
-                                                : 1;
+                    : 2 * units_fwd < 3 * simds              ? 6
+                    : units_fwd < 3 * simds                  ? 2
+                                                             : 1;
   }
   // a tiling given by the caller: every point group split over node_groups
-  if (p->opts.node_groups >= 2) small_G = p->opts.node_groups;
+  if (p->opts.node_groups >= 2) small_G = res_G = p->opts.node_groups;
   // Where every lane runs one node, the two node forms do not pay for their
   // costlier constants and the scalar record loads that a wave waits for at its
   // first node: the one-form kernels.  us a call, two forms / one: 10 smeared items
@@ -1066,8 +1080,6 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     const int64_t nq = p->q_off[s + 1] - p->q_off[s];
     const int N = (int)(p->row_off[b + 1] - p->row_off[b]) - 2;
     const int K = p->dqq[s] > 0.0 ? kSmearNodes : 1;
-    const int bk = bucket_of(N);
-    const int64_t rsz = 4 + 4 * (N + 2);
     p->out_off[b + 1] = p->out_off[b] + nq;
     ll_first[b] = (int64_t)ll_offs.size();
     {
@@ -1085,72 +1097,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       ll_count[b] = (int32_t)(ll_offs.size() - (size_t)ll_first[b]);
     }
     p->max_rows = std::max(p->max_rows, N + 2);
-    if (bk == kDeepBucket) {
-      // one unit per data point; its lanes split the layers
-      gr_first[b] = (int64_t)gr_offs.size();
-      gr_count[b] = (int32_t)nq;
-      const int ch64 = (N + 1 + 63) / 64;
-      const int cls = ch64 <= 8 ? 0 : ch64 <= 16 ? 1 : 2;
-      scan_ch[cls] = std::max(scan_ch[cls], ch64);
-      for (int64_t k = 0; k < nq; ++k) {
-        grad_units[kDeepBucket + cls].push_back({b, (int32_t)k, rec_gr, (double)K * (N + 1) * 64});
-        gr_offs.push_back(rec_gr);
-        rec_gr += rsz;
-      }
-      continue;
-    }
-    if (K > 1 && small_G >= 2) {
-      // every point group split over small_G node groups (lane = g npts + p)
-      const int npts = kWuPoints / small_G;
-      gr_first[b] = (int64_t)gr_offs.size();
-      int32_t cnt = 0;
-      for (int64_t p0 = 0; p0 < nq; p0 += npts) {
-        const int np = (int)std::min<int64_t>(npts, nq - p0);
-        Wu u{b, (int32_t)p0, rec_gr, (double)np * K * (N + 1)};
-        u.split = np | (small_G << 16);
-        split_units[bk].push_back(u);
-        gr_offs.push_back(rec_gr);
-        rec_gr += rsz;
-        ++cnt;
-      }
-      gr_count[b] = cnt;
-      continue;
-    }
-    const int nfull = (int)(nq / kWuPoints);
-    const int ntail = (int)(nq % kWuPoints);
-    gr_first[b] = (int64_t)gr_offs.size();
-    gr_count[b] = nfull + (ntail > 0 ? 1 : 0);
-    for (int k = 0; k < nfull; ++k) {
-      grad_units[bk].push_back({b, k * kWuPoints, rec_gr, (double)kWuPoints * K * (N + 1)});
-      gr_offs.push_back(rec_gr);
-      rec_gr += rsz;
-    }
-    if (ntail > 0) {
-      // A smeared tail gets a wave of its own: of 32 points or fewer with
-      // node groups x points over the lanes, else with idle lanes.  Its
-      // item stays wave-uniform, and no wave runs all 17 nodes for a few
-      // points.  Packing tails of several items into one wave (per-lane
-      // layer records, up to 1 KB of spill in the deep kernels, and launches
-      // of few waves that each take as long as a full unit) was the rule
-      // beyond 10 layers: 2048 ragged items 8.9 -> 6.6 ms, 200 items 5.3 ->
-      // 3.4 ms, 16384 items 38.0 -> 37.0 ms, FP32 5.6 -> 4.2 ms for 2048.
-      // Unsmeared tails, one node each, are still packed.
-      const int G = std::min(kWuPoints / ntail, K);
-      if ((p->opts.split_tails & NR_TAILS_LONE) && (ntail >= 48 || (K > 1 && G == 1))) {
-        grad_units[bk].push_back({b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)});
-      } else if ((p->opts.split_tails & NR_TAILS_SPLIT) && G >= 2) {
-        Wu u{b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)};
-        u.split = ntail | (G << 16);
-        split_units[bk].push_back(u);
-      } else {
-        tails[{N, K}].push_back({b, nfull * kWuPoints, ntail, rec_gr});
-      }
-      gr_offs.push_back(rec_gr);
-      rec_gr += rsz;
-    }
   }
   p->rec_ll_total = rec_ll;
-  p->rec_grad_total = rec_gr;
 
   hipError_t e = hipSuccess;
   auto keep = [&](void* ptr) { p->owned.push_back(ptr); };
@@ -1177,89 +1125,12 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     if (e == hipSuccess) { e = upload(&p->d_row_kind, kind); keep(p->d_row_kind); }
   }
   upload_lists(p->lists_ll, ll_first, ll_count, ll_offs);
-  upload_lists(p->lists_grad, gr_first, gr_count, gr_offs);
   if (e == hipSuccess) {
     std::vector<double> rule(p->node_t, p->node_t + kSmearNodes);
     rule.insert(rule.end(), p->node_w, p->node_w + kSmearNodes);
     append_math_tables(rule);
     e = upload(&p->d_rule, rule);
     keep(p->d_rule);
-  }
-
-  std::vector<Launch> tail_launches;  // after the full units
-  // tail launches: per (depth, nodes) group, largest tails first, first fit
-  // into 64-lane units; then one launch per bucket over all its groups (the
-  // units holding a single item join the full units below)
-  {
-    std::vector<std::vector<int32_t>> b_item(kNumBuckets), b_litem(kNumBuckets), b_lpt(kNumBuckets);
-    std::vector<std::vector<int64_t>> b_lrec(kNumBuckets);
-    int b_nodes[kNumBuckets] = {};
-    for (auto& kv : tails) {
-      const int bk = bucket_of(kv.first.first);
-      b_nodes[bk] = std::max(b_nodes[bk], kv.first.second);
-      auto& v = kv.second;
-      std::stable_sort(v.begin(), v.end(),
-                       [](const Tail& x, const Tail& y) { return x.count > y.count; });
-      std::vector<int> fill;                   // lanes used per unit of this group
-      std::vector<std::vector<size_t>> units;  // the tails of each unit
-      for (size_t t = 0; t < v.size(); ++t) {
-        size_t u = p->opts.pack_tails ? 0 : fill.size();
-        while (u < fill.size() && fill[u] + v[t].count > kWuPoints) ++u;
-        if (u == fill.size()) {
-          fill.push_back(0);
-          units.emplace_back();
-        }
-        units[u].push_back(t);
-        fill[u] += v[t].count;
-      }
-      for (const auto& un : units) {
-        if (un.size() == 1) {
-          // a unit of one item is a full unit with idle lanes (its layer
-          // records stay scalar loads)
-          const Tail& t = v[un[0]];
-          grad_units[bk].push_back(
-              {t.item, t.p0, t.rec0, (double)t.count * kv.first.second * (kv.first.first + 1)});
-          continue;
-        }
-        const size_t base = b_item[bk].size() * kWuPoints;
-        b_item[bk].push_back(v[un[0]].item);
-        b_litem[bk].insert(b_litem[bk].end(), kWuPoints, -1);
-        b_lpt[bk].insert(b_lpt[bk].end(), kWuPoints, 0);
-        b_lrec[bk].insert(b_lrec[bk].end(), kWuPoints, -1);
-        int f = 0;
-        for (size_t ti : un) {
-          const Tail& t = v[ti];
-          for (int l = 0; l < t.count; ++l) {
-            b_litem[bk][base + f + l] = t.item;
-            b_lpt[bk][base + f + l] = t.p0 + l;
-            b_lrec[bk][base + f + l] = t.rec0;
-          }
-          f += t.count;
-        }
-      }
-    }
-    for (int bk = kNumBuckets - 1; bk >= 0; --bk) {
-      if (b_item[bk].empty() || e != hipSuccess) continue;
-      // idle lanes repeat lane 0 of their unit (a valid point, result unused)
-      for (size_t u = 0; u < b_item[bk].size(); ++u)
-        for (int l = 0; l < kWuPoints; ++l)
-          if (b_litem[bk][u * kWuPoints + l] < 0) {
-            b_litem[bk][u * kWuPoints + l] = b_litem[bk][u * kWuPoints];
-            b_lpt[bk][u * kWuPoints + l] = b_lpt[bk][u * kWuPoints];
-          }
-      Launch L;
-      L.bucket = bk;
-      L.form = p->bucket_form[bk] == kFormSelect ? kFormRecompute : p->bucket_form[bk];
-      L.tail = true;
-      L.n_wu = (int)b_item[bk].size();
-      L.est = launch_estimate(p->precision, kBucketLmax[bk], L.n_wu, b_nodes[bk], simds);
-      e = upload(&L.item, b_item[bk]);
-      keep(L.item);
-      if (e == hipSuccess) { e = upload(&L.lane_item, b_litem[bk]); keep(L.lane_item); }
-      if (e == hipSuccess) { e = upload(&L.lane_pt, b_lpt[bk]); keep(L.lane_pt); }
-      if (e == hipSuccess) { e = upload(&L.lane_rec, b_lrec[bk]); keep(L.lane_rec); }
-      tail_launches.push_back(L);
-    }
   }
 
   // full-unit launches: one per non-empty bucket, deepest first, LPT order
@@ -1344,47 +1215,211 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
                      (split || (int64_t)all[0].size() <= 2 * simds || steps >= 1300 * (int64_t)nI);
     make_full(kOpLoglik, all, p->launches_fwd, split);
   }
-  make_full(kOpLoglikGrad, grad_units, p->launches_grad, false);
-  make_full(kOpLoglikGrad, split_units, p->launches_grad, true);
-  p->launches_grad.insert(p->launches_grad.end(), tail_launches.begin(), tail_launches.end());
-  for (const Launch& L : p->launches_grad) {
-    p->grad_scaled |= L.form == kFormSelect;
-    p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
-  }
-  // A launch that does not fill the device, or the last waves of one that
-  // does, leave it idle until the next launch of their stream; launches on
-  // other streams fill it.  The longest launches come first, each on the
-  // stream with the least work so far.  Measured on MI355X, two streams in
-  // the old order -> four in this one, ragged batches of 2..40 layers: 200
-  // items 3.37 -> 0.87 ms (with node groups chosen for it), 700: 4.1 -> 2.9,
-  // 2048: 6.5 -> 5.0, 2048 in FP32 4.2 -> 3.1.  A plan of many units per SIMD
-  // spends little on such gaps and loses more where kernels of different
-  // register budgets mix on a SIMD (16384 items in FP32 22.5 -> 23.4 ms, in
-  // FP64 36.9 both): it keeps two streams, alternating from bucket to bucket,
-  // with the small launches beside them.
-  if (e == hipSuccess && p->opts.side_stream && p->launches_grad.size() > 1) {
-    int64_t total = 0;
-    for (const Launch& L : p->launches_grad) total += L.n_wu;
-    if (total > 48 * simds) {
-      int full = 0;
-      for (Launch& L : p->launches_grad) {
-        const bool whole = !L.tail && !L.split;
-        L.side = whole ? full++ % 2 : L.n_wu <= 2 * simds ? 1 : 0;
-        p->n_side = std::max(p->n_side, L.side);
+  // the gradient's schedule with every smeared point group split over small_G
+  // node groups (1: whole groups of 64 points and tails)
+  auto build_grad = [&](int small_G, GradSchedule& S) {
+    std::vector<std::vector<Wu>> grad_units(kNumBuckets + kDeepClasses);
+    std::vector<std::vector<Wu>> split_units(kNumBuckets);
+    std::map<std::pair<int, int>, std::vector<Tail>> tails;  // (depth, nodes)
+    std::vector<int64_t> gr_first(nI), gr_offs;
+    std::vector<int32_t> gr_count(nI);
+    int64_t rec_gr = 0;
+    for (int b = 0; b < nI; ++b) {
+      const int s = p->dataset_of_item[b];
+      const int64_t nq = p->q_off[s + 1] - p->q_off[s];
+      const int N = (int)(p->row_off[b + 1] - p->row_off[b]) - 2;
+      const int K = p->dqq[s] > 0.0 ? kSmearNodes : 1;
+      const int bk = bucket_of(N);
+      const int64_t rsz = 4 + 4 * (N + 2);
+      if (bk == kDeepBucket) {
+        // one unit per data point; its lanes split the layers
+        gr_first[b] = (int64_t)gr_offs.size();
+        gr_count[b] = (int32_t)nq;
+        const int ch64 = (N + 1 + 63) / 64;
+        const int cls = ch64 <= 8 ? 0 : ch64 <= 16 ? 1 : 2;
+        scan_ch[cls] = std::max(scan_ch[cls], ch64);
+        for (int64_t k = 0; k < nq; ++k) {
+          grad_units[kDeepBucket + cls].push_back({b, (int32_t)k, rec_gr, (double)K * (N + 1) * 64});
+          gr_offs.push_back(rec_gr);
+          rec_gr += rsz;
+        }
+        continue;
       }
-    } else {
-      std::stable_sort(p->launches_grad.begin(), p->launches_grad.end(),
-                       [](const Launch& x, const Launch& y) { return x.est > y.est; });
-      double load[1 + kSideStreams] = {};
-      for (Launch& L : p->launches_grad) {
-        L.side = (int)(std::min_element(load, load + 1 + kSideStreams) - load);
-        load[L.side] += L.est;
-        p->n_side = std::max(p->n_side, L.side);
+      if (K > 1 && small_G >= 2) {
+        // every point group split over small_G node groups (lane = g npts + p)
+        const int npts = kWuPoints / small_G;
+        gr_first[b] = (int64_t)gr_offs.size();
+        int32_t cnt = 0;
+        for (int64_t p0 = 0; p0 < nq; p0 += npts) {
+          const int np = (int)std::min<int64_t>(npts, nq - p0);
+          Wu u{b, (int32_t)p0, rec_gr, (double)np * K * (N + 1)};
+          u.split = np | (small_G << 16);
+          split_units[bk].push_back(u);
+          gr_offs.push_back(rec_gr);
+          rec_gr += rsz;
+          ++cnt;
+        }
+        gr_count[b] = cnt;
+        continue;
+      }
+      const int nfull = (int)(nq / kWuPoints);
+      const int ntail = (int)(nq % kWuPoints);
+      gr_first[b] = (int64_t)gr_offs.size();
+      gr_count[b] = nfull + (ntail > 0 ? 1 : 0);
+      for (int k = 0; k < nfull; ++k) {
+        grad_units[bk].push_back({b, k * kWuPoints, rec_gr, (double)kWuPoints * K * (N + 1)});
+        gr_offs.push_back(rec_gr);
+        rec_gr += rsz;
+      }
+      if (ntail > 0) {
+        // A smeared tail gets a wave of its own: of 32 points or fewer with
+        // node groups x points over the lanes, else with idle lanes.  Its
+        // item stays wave-uniform, and no wave runs all 17 nodes for a few
+        // points.  Packing tails of several items into one wave (per-lane
+        // layer records, up to 1 KB of spill in the deep kernels, and launches
+        // of few waves that each take as long as a full unit) was the rule
+        // beyond 10 layers: 2048 ragged items 8.9 -> 6.6 ms, 200 items 5.3 ->
+        // 3.4 ms, 16384 items 38.0 -> 37.0 ms, FP32 5.6 -> 4.2 ms for 2048.
+        // Unsmeared tails, one node each, are still packed.
+        const int G = std::min(kWuPoints / ntail, K);
+        if ((p->opts.split_tails & NR_TAILS_LONE) && (ntail >= 48 || (K > 1 && G == 1))) {
+          grad_units[bk].push_back({b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)});
+        } else if ((p->opts.split_tails & NR_TAILS_SPLIT) && G >= 2) {
+          Wu u{b, nfull * kWuPoints, rec_gr, (double)ntail * K * (N + 1)};
+          u.split = ntail | (G << 16);
+          split_units[bk].push_back(u);
+        } else {
+          tails[{N, K}].push_back({b, nfull * kWuPoints, ntail, rec_gr});
+        }
+        gr_offs.push_back(rec_gr);
+        rec_gr += rsz;
       }
     }
-    if (p->n_side > 0) e = side_pool_acquire(p->device, p->n_side);
-    p->pooled = p->n_side > 0 && e == hipSuccess;
-  }
+    S.records = rec_gr;
+    upload_lists(S.lists, gr_first, gr_count, gr_offs);
+
+    std::vector<Launch> tail_launches;  // after the full units
+    // tail launches: per (depth, nodes) group, largest tails first, first fit
+    // into 64-lane units; then one launch per bucket over all its groups (the
+    // units holding a single item join the full units below)
+    {
+      std::vector<std::vector<int32_t>> b_item(kNumBuckets), b_litem(kNumBuckets), b_lpt(kNumBuckets);
+      std::vector<std::vector<int64_t>> b_lrec(kNumBuckets);
+      int b_nodes[kNumBuckets] = {};
+      for (auto& kv : tails) {
+        const int bk = bucket_of(kv.first.first);
+        b_nodes[bk] = std::max(b_nodes[bk], kv.first.second);
+        auto& v = kv.second;
+        std::stable_sort(v.begin(), v.end(),
+                         [](const Tail& x, const Tail& y) { return x.count > y.count; });
+        std::vector<int> fill;                   // lanes used per unit of this group
+        std::vector<std::vector<size_t>> units;  // the tails of each unit
+        for (size_t t = 0; t < v.size(); ++t) {
+          size_t u = p->opts.pack_tails ? 0 : fill.size();
+          while (u < fill.size() && fill[u] + v[t].count > kWuPoints) ++u;
+          if (u == fill.size()) {
+            fill.push_back(0);
+            units.emplace_back();
+          }
+          units[u].push_back(t);
+          fill[u] += v[t].count;
+        }
+        for (const auto& un : units) {
+          if (un.size() == 1) {
+            // a unit of one item is a full unit with idle lanes (its layer
+            // records stay scalar loads)
+            const Tail& t = v[un[0]];
+            grad_units[bk].push_back(
+                {t.item, t.p0, t.rec0, (double)t.count * kv.first.second * (kv.first.first + 1)});
+            continue;
+          }
+          const size_t base = b_item[bk].size() * kWuPoints;
+          b_item[bk].push_back(v[un[0]].item);
+          b_litem[bk].insert(b_litem[bk].end(), kWuPoints, -1);
+          b_lpt[bk].insert(b_lpt[bk].end(), kWuPoints, 0);
+          b_lrec[bk].insert(b_lrec[bk].end(), kWuPoints, -1);
+          int f = 0;
+          for (size_t ti : un) {
+            const Tail& t = v[ti];
+            for (int l = 0; l < t.count; ++l) {
+              b_litem[bk][base + f + l] = t.item;
+              b_lpt[bk][base + f + l] = t.p0 + l;
+              b_lrec[bk][base + f + l] = t.rec0;
+            }
+            f += t.count;
+          }
+        }
+      }
+      for (int bk = kNumBuckets - 1; bk >= 0; --bk) {
+        if (b_item[bk].empty() || e != hipSuccess) continue;
+        // idle lanes repeat lane 0 of their unit (a valid point, result unused)
+        for (size_t u = 0; u < b_item[bk].size(); ++u)
+          for (int l = 0; l < kWuPoints; ++l)
+            if (b_litem[bk][u * kWuPoints + l] < 0) {
+              b_litem[bk][u * kWuPoints + l] = b_litem[bk][u * kWuPoints];
+              b_lpt[bk][u * kWuPoints + l] = b_lpt[bk][u * kWuPoints];
+            }
+        Launch L;
+        L.bucket = bk;
+        L.form = p->bucket_form[bk] == kFormSelect ? kFormRecompute : p->bucket_form[bk];
+        L.tail = true;
+        L.n_wu = (int)b_item[bk].size();
+        L.est = launch_estimate(p->precision, kBucketLmax[bk], L.n_wu, b_nodes[bk], simds);
+        e = upload(&L.item, b_item[bk]);
+        keep(L.item);
+        if (e == hipSuccess) { e = upload(&L.lane_item, b_litem[bk]); keep(L.lane_item); }
+        if (e == hipSuccess) { e = upload(&L.lane_pt, b_lpt[bk]); keep(L.lane_pt); }
+        if (e == hipSuccess) { e = upload(&L.lane_rec, b_lrec[bk]); keep(L.lane_rec); }
+        tail_launches.push_back(L);
+      }
+    }
+
+    make_full(kOpLoglikGrad, grad_units, S.launches, false);
+    make_full(kOpLoglikGrad, split_units, S.launches, true);
+    S.launches.insert(S.launches.end(), tail_launches.begin(), tail_launches.end());
+    for (const Launch& L : S.launches) {
+      p->grad_scaled |= L.form == kFormSelect;
+      p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
+    }
+    // A launch that does not fill the device, or the last waves of one that
+    // does, leave it idle until the next launch of their stream; launches on
+    // other streams fill it.  The longest launches come first, each on the
+    // stream with the least work so far.  Measured on MI355X, two streams in
+    // the old order -> four in this one, ragged batches of 2..40 layers: 200
+    // items 3.37 -> 0.87 ms (with node groups chosen for it), 700: 4.1 -> 2.9,
+    // 2048: 6.5 -> 5.0, 2048 in FP32 4.2 -> 3.1.  A plan of many units per SIMD
+    // spends little on such gaps and loses more where kernels of different
+    // register budgets mix on a SIMD (16384 items in FP32 22.5 -> 23.4 ms, in
+    // FP64 36.9 both): it keeps two streams, alternating from bucket to bucket,
+    // with the small launches beside them.
+    if (e == hipSuccess && p->opts.side_stream && S.launches.size() > 1) {
+      int64_t total = 0;
+      for (const Launch& L : S.launches) total += L.n_wu;
+      if (total > 48 * simds) {
+        int full = 0;
+        for (Launch& L : S.launches) {
+          const bool whole = !L.tail && !L.split;
+          L.side = whole ? full++ % 2 : L.n_wu <= 2 * simds ? 1 : 0;
+          S.n_side = std::max(S.n_side, L.side);
+        }
+      } else {
+        std::stable_sort(S.launches.begin(), S.launches.end(),
+                         [](const Launch& x, const Launch& y) { return x.est > y.est; });
+        double load[1 + kSideStreams] = {};
+        for (Launch& L : S.launches) {
+          L.side = (int)(std::min_element(load, load + 1 + kSideStreams) - load);
+          load[L.side] += L.est;
+          S.n_side = std::max(S.n_side, L.side);
+        }
+      }
+    }
+  };
+  build_grad(small_G, p->grad);
+  p->res_own = res_G != small_G;
+  if (p->res_own) build_grad(res_G, p->grad_res);
+  const int n_side = std::max(p->grad.n_side, p->grad_res.n_side);
+  if (n_side > 0 && e == hipSuccess) e = side_pool_acquire(p->device, n_side);
+  p->pooled = n_side > 0 && e == hipSuccess;
   for (int c = 0; c < kDeepClasses && e == hipSuccess; ++c)
     if (scan_ch[c] > 0) e = prepare_grad_scan(scan_ch[c]);
   if (e == hipSuccess) e = prepare_reduce(p->max_rows);
@@ -1763,7 +1798,7 @@ nr_status nr_plan_launches(const nr_plan* p, int32_t op, int32_t capacity, nr_la
                 "the header's launch kinds and the kernels' disagree");
   static_assert(NR_NUM_BUCKETS == kDeepBucket, "the deep stacks' launches follow the buckets");
   const bool grad = op == NR_OP_LOGLIK_GRAD;
-  const std::vector<Launch>& list = grad ? p->launches_grad : p->launches_fwd;
+  const std::vector<Launch>& list = grad ? p->grad.launches : p->launches_fwd;
   *n_out = (int32_t)list.size();
   for (int32_t k = 0; k < capacity && k < *n_out; ++k) {
     const Launch& L = list[k];

@@ -68,3 +68,18 @@ def test_value_form_of_items_of_little_work(nr, orc, L, nq, items, forms):
         check_R(R[b], Ro)
         llo = orc.loglik(batch.rows_of(b), 0.97, 1.3e-7, Q, Robs, e, d)
         check_logL(ll[b], llo, logL_bound(Ro, Robs, e))
+
+
+def test_resolution_calls_of_two_units_per_simd_are_not_split(nr):
+    import torch
+    batch = _batch(6, 84, 1024)
+    p = nr.Problem.from_batch(batch)
+    assert {x["mode"] for x in p.plan.launches()} == {nr._n.NR_MODE_SPLIT}
+    whole = nr.Problem.from_batch(batch, options={"split_tails": 3})
+    assert {x["mode"] for x in whole.plan.launches()} == {nr._n.NR_MODE_FULL, nr._n.NR_MODE_SPLIT}
+    for x, y in zip(p.loglik_grad_res(), whole.loglik_grad_res()):
+        assert torch.equal(x, y)
+    # the plain call's records and the other schedule's share the workspace
+    want = [t.clone() for t in p.loglik_grad()]
+    p.loglik_grad_res()
+    assert all(torch.equal(x, y) for x, y in zip(p.loglik_grad(), want))
