@@ -201,7 +201,8 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *     by its plans, and a set of the plan's own for captured calls), forked
  *     from the caller's stream after the per-layer constants and joined back
  *     before the reduction: small launches run beside others instead of
- *     leaving most of the device idle, and consecutive ones overlap;
+ *     leaving most of the device idle, and consecutive ones overlap; launches
+ *     that are done sooner in a row than a fork takes stay on the caller's;
  *     0 keeps every launch on the caller's stream.  The fork and join are
  *     event waits, so calls stay ordered on the caller's stream and can be
  *     captured into a HIP graph (the side streams join the capture).  Calls

@@ -223,11 +223,14 @@ struct SidePool {
 };
 SidePool g_side_pool[kMaxDevices];
 
-hipError_t side_pool_acquire(int device, int n) {
+// (All its streams are made together: one made later, after others of the process,
+// would share a hardware queue with one of them, and 6 to 20 ragged items would take
+// 1.2-1.5 times as long.)
+hipError_t side_pool_acquire(int device) {
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
   SidePool& pool = g_side_pool[device];
   std::lock_guard<std::mutex> lock(pool.mu);
-  const hipError_t e = fork_join_make(pool.set, n);
+  const hipError_t e = fork_join_make(pool.set, kSideStreams);
   if (e == hipSuccess)
     ++pool.users;
   else if (pool.users == 0)
@@ -493,6 +496,59 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
     }
   }
   return best_G;
+}
+
+// The streams of a schedule's launches.  A launch that does not fill the device,
+// or the last waves of one that does, leave it idle until the next launch of their
+// stream; launches on other streams fill it.  The longest launches come first, each
+// on the stream with the least work so far.  Measured on MI355X, two streams in the
+// old order -> four in this one, ragged batches of 2..40 layers: 200 items 3.37 ->
+// 0.87 ms (with node groups chosen for it), 700: 4.1 -> 2.9, 2048: 6.5 -> 5.0, 2048 in
+// FP32 4.2 -> 3.1.  Three exceptions:
+//  * A plan of many units per SIMD spends little on such gaps and loses more where
+//    kernels of different register budgets mix on a SIMD (16384 items in FP32 22.5 ->
+//    23.4 ms, in FP64 36.9 both): it keeps two streams, alternating from bucket to
+//    bucket, with the small launches beside them.
+//  * Split and packed launches of more than three waves per SIMD fill the device
+//    alone and stay on the caller's stream (beside / after, us a call: 4096 draws of
+//    10 layers x 400 points, 4096 split units 2254 / 2225, x 80 points 552 / 518, 28
+//    layers x 90 points 2066 / 1993; but 2300 draws, 2300 split units 1279 / 1309, 28
+//    layers x 90 points, 1100 split units 686 / 979).
+//  * A call that forks takes some 55 us however short its kernels are (events and
+//    waits, on the host and across hardware queues), so launches that are done by
+//    then in a row stay in a row: two items of 20 and 2 layers 46.6 us in a row, 48-57
+//    on two streams; two of 28 and 6 60.5 / 55.3.
+constexpr double kForkCallUs = 55.0, kLaunchUs = 5.0;
+void assign_streams(GradSchedule& S, bool side, int precision, int64_t simds) {
+  std::vector<Launch>& list = S.launches;
+  S.n_side = 0;
+  if (!side || list.size() < 2) return;
+  int64_t total = 0;
+  double us = 0.0;
+  for (const Launch& L : list) {
+    total += L.n_wu;
+    // (us per unit of the estimates, from the calls above)
+    us += (precision == NR_F32 ? 0.30 : 0.45) * L.est + kLaunchUs;
+  }
+  if (us <= kForkCallUs) return;
+  if (total > 48 * simds) {
+    int full = 0;
+    for (Launch& L : list) {
+      const bool whole = !L.tail && !L.split;
+      L.side = whole ? full++ % 2 : L.n_wu <= 2 * simds ? 1 : 0;
+      S.n_side = std::max(S.n_side, L.side);
+    }
+    return;
+  }
+  std::stable_sort(list.begin(), list.end(),
+                   [](const Launch& x, const Launch& y) { return x.est > y.est; });
+  double load[1 + kSideStreams] = {};
+  for (Launch& L : list) {
+    const bool large = (L.tail || L.split) && L.n_wu > 3 * simds;
+    L.side = large ? 0 : (int)(std::min_element(load, load + 1 + kSideStreams) - load);
+    load[L.side] += L.est;
+    S.n_side = std::max(S.n_side, L.side);
+  }
 }
 
 nr_status run_launches(const nr_plan* p, int op, KernelArgs a, hipStream_t st,
@@ -1381,45 +1437,15 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       p->grad_scaled |= L.form == kFormSelect;
       p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
     }
-    // A launch that does not fill the device, or the last waves of one that
-    // does, leave it idle until the next launch of their stream; launches on
-    // other streams fill it.  The longest launches come first, each on the
-    // stream with the least work so far.  Measured on MI355X, two streams in
-    // the old order -> four in this one, ragged batches of 2..40 layers: 200
-    // items 3.37 -> 0.87 ms (with node groups chosen for it), 700: 4.1 -> 2.9,
-    // 2048: 6.5 -> 5.0, 2048 in FP32 4.2 -> 3.1.  A plan of many units per SIMD
-    // spends little on such gaps and loses more where kernels of different
-    // register budgets mix on a SIMD (16384 items in FP32 22.5 -> 23.4 ms, in
-    // FP64 36.9 both): it keeps two streams, alternating from bucket to bucket,
-    // with the small launches beside them.
-    if (e == hipSuccess && p->opts.side_stream && S.launches.size() > 1) {
-      int64_t total = 0;
-      for (const Launch& L : S.launches) total += L.n_wu;
-      if (total > 48 * simds) {
-        int full = 0;
-        for (Launch& L : S.launches) {
-          const bool whole = !L.tail && !L.split;
-          L.side = whole ? full++ % 2 : L.n_wu <= 2 * simds ? 1 : 0;
-          S.n_side = std::max(S.n_side, L.side);
-        }
-      } else {
-        std::stable_sort(S.launches.begin(), S.launches.end(),
-                         [](const Launch& x, const Launch& y) { return x.est > y.est; });
-        double load[1 + kSideStreams] = {};
-        for (Launch& L : S.launches) {
-          L.side = (int)(std::min_element(load, load + 1 + kSideStreams) - load);
-          load[L.side] += L.est;
-          S.n_side = std::max(S.n_side, L.side);
-        }
-      }
-    }
+    assign_streams(S, p->opts.side_stream != 0, p->precision, simds);
   };
   build_grad(small_G, p->grad);
   p->res_own = res_G != small_G;
   if (p->res_own) build_grad(res_G, p->grad_res);
-  const int n_side = std::max(p->grad.n_side, p->grad_res.n_side);
-  if (n_side > 0 && e == hipSuccess) e = side_pool_acquire(p->device, n_side);
-  p->pooled = n_side > 0 && e == hipSuccess;
+  if (std::max(p->grad.n_side, p->grad_res.n_side) > 0 && e == hipSuccess) {
+    e = side_pool_acquire(p->device);
+    p->pooled = e == hipSuccess;
+  }
   for (int c = 0; c < kDeepClasses && e == hipSuccess; ++c)
     if (scan_ch[c] > 0) e = prepare_grad_scan(scan_ch[c]);
   if (e == hipSuccess) e = prepare_reduce(p->max_rows);

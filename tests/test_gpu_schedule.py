@@ -83,3 +83,22 @@ def test_resolution_calls_of_two_units_per_simd_are_not_split(nr):
     want = [t.clone() for t in p.loglik_grad()]
     p.loglik_grad_res()
     assert all(torch.equal(x, y) for x, y in zip(p.loglik_grad(), want))
+
+
+def _streams(p):
+    return [x["stream"] for x in p.plan.launches()]
+
+
+def test_split_launch_that_fills_the_device_stays_on_the_callers_stream(nr):
+    # 400 points: six whole units per item and a tail of 16, in a split launch
+    p = nr.Problem.from_batch(_batch(6, 400, 3072))
+    assert [(x["mode"], x["units"], x["stream"]) for x in p.plan.launches()] == [
+        (nr._n.NR_MODE_FULL, 6 * 3072, 0), (nr._n.NR_MODE_SPLIT, 3072, 1)]
+    p = nr.Problem.from_batch(_batch(6, 400, 3073))
+    assert _streams(p) == [0, 0]
+
+
+def test_launches_shorter_than_a_fork_stay_in_a_row(nr):
+    assert _streams(nr.Problem.from_batch(_batch([20, 2], 200, 2))) == [0, 0]
+    assert max(_streams(nr.Problem.from_batch(_batch([36, 28], 200, 2)))) == 1
+    assert max(_streams(nr.Problem.from_batch(_batch([40, 30, 20, 10], 300, 4)))) == 3
