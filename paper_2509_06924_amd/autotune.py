@@ -33,10 +33,16 @@ def default_cache_path():
                                        "autotune.json"))
 
 
+# What the options stand for; raised whenever a rule, a form or a kernel behind an
+# option changes, so that choices timed on others are timed again.
+SCHEDULES = 2
+
+
 def structure_key(q_off, row_off, dataset_of_item, precision, device_name=""):
     """Class of a batch structure: precision, the layer-count buckets present
     (with their share of the work rounded to tenths), points per item and
-    number of items on a log2 scale, and the device."""
+    number of items on a log2 scale, the device, the library's version and
+    the revision of its schedules."""
     q_off = np.asarray(q_off, np.int64)
     row_off = np.asarray(row_off, np.int64)
     dsi = np.asarray(dataset_of_item, np.int64)
@@ -60,6 +66,7 @@ def structure_key(q_off, row_off, dataset_of_item, precision, device_name=""):
         "log2_items": int(round(math.log2(n))) if n > 0 else 0,
         "device": device_name,
         "library": int(_n.lib().nr_version()),
+        "schedules": SCHEDULES,
     }, sort_keys=True)
 
 
