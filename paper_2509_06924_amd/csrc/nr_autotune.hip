@@ -6,10 +6,10 @@
 #include <algorithm>
 #include <chrono>
 #include <cstdint>
-#include <set>
 #include <vector>
 
 #include "nr.h"
+#include "nr_autotune.hpp"
 
 namespace {
 
@@ -137,18 +137,6 @@ extern "C" nr_status nr_autotune(const nr_batch_desc* d, const nr_values* v, int
   // any smeared dataset in use (the node-group tilings apply to them)
   bool smeared = false;
   for (int i = 0; i < d->n_items; ++i) smeared |= d->dq_over_q[d->dataset_of_item[i]] > 0.0;
-  // the buckets present that have both forms
-  std::set<int> used;
-  const int smax = nr_store_max_layers(d->precision);
-  for (int i = 0; i < d->n_items; ++i) {
-    const int L = (int)(d->row_off[i + 1] - d->row_off[i]) - 2;
-    for (int k = 0; k < NR_NUM_BUCKETS; ++k)
-      if (L <= nr_bucket_lmax(k)) {
-        if (nr_bucket_lmax(k) <= smax) used.insert(k);
-        break;
-      }
-  }
-
   nr_plan_options best = def;
   double best_ms = 0.0, def_ms = 0.0;
   nr_status st = time_options(d, v, best, b, reps, s, &best_ms);
@@ -165,12 +153,11 @@ extern "C" nr_status nr_autotune(const nr_batch_desc* d, const nr_values* v, int
     }
     return NR_OK;
   };
-  for (int k : used)
-    for (int var : {NR_VARIANT_STORE, NR_VARIANT_RECOMPUTE}) {
-      nr_plan_options o = best;
-      o.grad_variant[k] = var;
-      if ((st = consider(o)) != NR_OK) return st;
-    }
+  for (const auto& [k, var] : nr::form_candidates(d)) {
+    nr_plan_options o = best;
+    o.grad_variant[k] = var;
+    if ((st = consider(o)) != NR_OK) return st;
+  }
   for (int run : kXcdRuns)
     if (run != best.xcd_run) {
       nr_plan_options o = best;
