@@ -238,8 +238,9 @@ nr_status nr_plan_options_default(nr_plan_options* opts);
 
 /* Autotuner: chooses plan options for the batch structure *desc by timing
  * nr_loglik_grad on the caller's data `v` (device arrays, as for the
- * evaluation calls) under candidate schedules: per bucket present that has
- * both forms, the store and the recompute form; xcd_run 1, 4, 8, 16, 32;
+ * evaluation calls) under candidate schedules: per bucket present, the store
+ * form where it has one and the recompute form (NR_F32: where it has both; the
+ * last bucket stands for deep stacks too); xcd_run 1, 4, 8, 16, 32;
  * pack_tails, split_tails and side_stream toggled (coordinate search from the defaults,
  * after a 0.3 s warm-up).  A candidate replaces the current one only when its
  * median over `reps` timed calls is at least 3 % lower; a final interleaved
