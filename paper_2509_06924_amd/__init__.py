@@ -642,12 +642,14 @@ def _plain(problem, g_rows, g_inst, grad_out):
     memory and would be lost, and a dispatch mode (a tracer, an operation
     counter) would not see the launch."""
     import torch
-    import torch.autograd.forward_ad as forward_ad
+    forward_ad = torch.autograd.forward_ad
+    # (no dual level is open: no tensor has a tangent, and three calls are spared)
+    dual = forward_ad._current_level >= 0
     return (problem.plan.handle is not None
             and torch._C._len_torch_dispatch_stack() == 0
             and all(type(t) is torch.Tensor and torch._C._has_storage(t)
                     and not t._is_zerotensor() and not t.is_neg() and t.dtype == torch.float64
-                    and forward_ad.unpack_dual(t).tangent is None
+                    and not (dual and forward_ad.unpack_dual(t).tangent is not None)
                     and t.device == problem.device for t in (g_rows, g_inst, grad_out))
             and g_rows.is_contiguous() and g_inst.is_contiguous()
             and g_rows.shape == problem.layers.shape
