@@ -389,7 +389,8 @@ def main():
             "unit": "TFLOP/s",
             "frac": roof["frac"],
             "traffic": measured_traffic(args.workload) if args.precision == "f64" else None,
-            "kernel": "k_loglik_grad (layer product, smearing, logL and adjoint)",
+            "kernel": "the gradient launches (layer product, smearing, logL and adjoint): "
+                      "k_grad_select, k_loglik_grad, k_grad_scan_select by precision and depth",
             "kernel_ms": kern_s * 1e3,
             **{k: v for k, v in roof.items() if k not in ("achieved", "frac")},
         },

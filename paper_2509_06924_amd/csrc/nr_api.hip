@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -122,7 +123,7 @@ struct Launch {
   bool one[2] = {};    // split units whose one node is counted per lane: plain, resolution
   int scan_ch = 0;     // deep lists: the largest levels-per-lane of its items at 64 lanes
   int side = 0;        // 0: the caller's stream, k: the plan's side stream k - 1
-  double est = 0.0;    // gradient: estimated time (see launch_estimate)
+  double est = 0.0;    // gradient: estimated time, us (see launch_estimate)
   int n_wu = 0;
   int32_t* item = nullptr;      // [n_wu]: the unit's item (first item for tails)
   int32_t* split_code = nullptr;  // [n_wu] split units: points | node groups << 16
@@ -143,10 +144,10 @@ struct RecordLists {
 // Workgroups are dispatched to the 8 XCDs round-robin (block b -> XCD b % 8)
 // and each XCD has its own L2.  Block b takes entry xcd_order(b, n, run) of
 // the cost-sorted unit list: within each chunk of 8 x run blocks, one XCD
-// gets a run of `run` consecutive entries (the units of one item are
-// consecutive), so an item's layer records are fetched into one L2, while
-// the chunks keep the longest-first order.  The last partial chunk maps to
-// itself.
+// gets a run of `run` consecutive entries, while the chunks keep the
+// longest-first order: where equal costs leave the units of one item together
+// (see make_full), its layer records are fetched into one L2.  The last partial
+// chunk maps to itself.
 constexpr int kXcds = 8;
 size_t xcd_order(size_t b, size_t n, size_t run) {
   const size_t chunk = kXcds * run;
@@ -416,32 +417,55 @@ size_t op_doubles(const nr_plan* p, int op) {
   return n;
 }
 
-// Time of a gradient launch over `waves` units that run `nodes` nodes each, in
-// units of one level of one node at a full SIMD.  A wave runs its nodes and an
-// epilogue (one reduction per record field) worth e nodes, and w waves per
-// SIMD take f(w) times one wave's share of a full SIMD: s1 alone (nothing
-// hides its latencies), 2.1 up to two, then a little over w (the last wave's
-// wait), but not over two rounds of two up to four (676 items of 355 points, 12
-// layers, 3.96 waves: 480 us whole, 546 in three groups).  e and s1 are fits of measured calls (MI355X, 7 to 7168 units of 64
-// points at every G): 0.6 and 1.4 for the kernels at two waves per SIMD (10
-// layers), 1.35 and 1.16 at one (24 layers), whose levels cost 1.26 as much
-// and whose split waves go round by round (24 layers, G = 2, 2.5 / 3.2 / 3.7 /
-// 4.4 / 5.2 / 6.4 waves per SIMD take 3.1 / 4.2 / 4.1 / 5.0 / 6.0 / 7.0).
-// Shallow (676 items of 355 points, 1 layer: 64.6 whole, 71 / 73 / 106 us at G =
-// 2 / 3 / 9) and FP32 nodes are shorter beside the same epilogue, e = 2; in FP32 two to three
-// waves take as long as 3.3 (20 to 4000 units of 5, 12, 20 and 26 layers).
-double launch_estimate(int precision, int lmax, int64_t waves, int nodes, int64_t simds) {
-  const bool one_wave = grad_waves_per_simd(precision, lmax) == 1;
-  const bool f32 = precision == NR_F32 && !one_wave;
-  const double e = f32 || lmax < kSelectMinLayers ? 2.0 : one_wave ? 1.35 : 0.6, s1 = one_wave ? 1.16 : 1.4;
-  const double w = (double)waves / (double)simds;
-  const double f = w <= 1.0              ? s1
-                   : w <= 2.0            ? 2.1
-                   : one_wave            ? (nodes < kSmearNodes ? std::ceil(w) : w + 0.2)
-                   : f32                 ? std::max(3.3, w + 0.6)
-                   : w <= 4.0            ? std::min(w + 0.6, 4.2)
-                                         : w + 0.2;
-  return f * (nodes + e) * (lmax + 1) * (one_wave ? 1.26 : 1.0);
+// What a gradient launch costs, in us.  A wave runs its nodes and an epilogue (one
+// reduction per record field) worth `e` nodes more, `us` per level each; w waves per
+// SIMD take f(w) times a wave's share of a full SIMD.  A SIMD with one wave more than
+// the others holds up the launch, so f goes in steps: s1 up to one wave (nothing
+// hides its latencies), 2 up to two, s3 up to three, then `slope` for each.  Fits of
+// calls of uniform items (MI355X, 0.5 to 8 units per SIMD in 1, 2, 3, 4, 6, 9 and 17 node
+// groups at every bucket's depth; us a call = 9 + the launch), to 4 % in the mean and
+// 10-20 % at worst: 10 layers FP64 at 1.98 / 2.30 / 2.98 / 3.40 / 5.98 units per SIMD 209
+// / 285 / 304 / 371 / 610 whole, 120 / 166 / 173 / 210 / 338 in two groups; 36 layers
+// whole at 0.98 / 1.20 / 1.98 / 2.30 519 / 852 / 963 / 1324.
+struct LaunchCost {
+  double us, e;             // per level and node; the epilogue in nodes
+  double s1, s3, slope;     // f(w)
+  double step(double w) const {
+    const double c = std::ceil(w);
+    return c <= 1.0 ? s1 : (c <= 2.0 ? 2.0 : s3 + (c - 3.0) * slope) - 0.1 * (c - w);
+  }
+};
+LaunchCost launch_cost(int precision, int lmax, bool res, bool split) {
+  const bool f64 = precision == NR_F64;
+  const double n = lmax + 1;
+  if (grad_waves_per_simd(precision, lmax) == 1)
+    return f64 ? LaunchCost{(0.51 + 0.0065 * (lmax - 16)) * (res ? 1.1 : 1.0), res ? 1.25 : 1.55,
+                            1.05, 3.0, 0.97}
+               : LaunchCost{0.40, res ? 1.85 : 2.1, 0.98, 2.97, 0.96};
+  if (f64) {
+    // (the whole resolution kernels spill less than the split ones: 0.8 of the time
+    // at 14 layers)
+    const double whole = split       ? 1.0
+                         : lmax <= 2 ? 1.04
+                         : res       ? 1.0 - 0.024 * std::max(0, lmax - 6)
+                                     : 1.0;
+    return {(0.35 + 0.012 * lmax) * (res ? 1.25 : 1.0) * whole, res ? 0.6 + 5.0 / n : 0.85 + 6.5 / n,
+            split ? 1.38 : 1.25, lmax <= 2 ? 2.72 : 2.97,
+            lmax <= 2 ? 0.8 : split ? 0.86 : res ? 0.93 : 1.0};
+  }
+  // (16 layers: the split resolution kernel has the SIMD to itself)
+  if (res && split && lmax == 16) return {0.38, 2.1, 0.95, 2.98, 0.96};
+  const double whole =
+      split ? 1.0 : lmax <= 2 ? 1.14 : lmax <= 6 ? 1.1 : lmax <= 20 ? 1.04 : lmax <= 24 ? 0.93 : 0.85;
+  return {(0.19 + 0.006 * lmax) * (res && lmax <= 6 ? 1.3 : 1.0) * whole,
+          std::min(6.0, std::max(2.0, res ? 0.7 + 12.0 / n : 1.0 + 15.0 / n)),
+          split ? 1.42 : 1.34, lmax <= 4 || (lmax == 10 && !res && !split) ? 2.65 : 3.05,
+          lmax <= 4 ? 0.73 : 0.86};
+}
+double launch_estimate(int precision, int lmax, bool split, int64_t waves, double nodes,
+                       int64_t simds) {
+  const LaunchCost c = launch_cost(precision, lmax, false, split);
+  return c.us * (lmax + 1) * (nodes + c.e) * c.step((double)waves / (double)simds);
 }
 
 // Whether a gradient launch of one node per lane counts it per lane.  A wave alone
@@ -460,68 +484,143 @@ bool lane_counter_pays(int precision, int lmax, bool res, int64_t waves, int64_t
   return (few && lmax != 6) || (lmax >= 16 && lmax != 18 && (!res || lmax <= 28));
 }
 
-// Node groups per point for the gradient of a small plan: the G whose launches
-// (one per depth bucket, on up to 1 + kSideStreams streams) take the least
-// estimated time.  Units of 400 points, 10 layers, us a call at G = 1 / 2 / 3 /
-// 6 / 9 / 17: 112 units 141 / 80 / 62 / 42 / 38 / 51; 672: 146 / 120 / 92 / 94 /
-// 104 / 153; 1344: 212 / 170 / 156 / 166 / 176 / 278; 2688: 309 / 268 / 283 /
-// 298 / 328 / 537; 4480: 430 / 445 / 446 / 479 / 535 / 878.  G = 2048 / units,
-// the rule before, took 53, 92, 211, 309 and 429 us there.
+// How a small plan's gradient units are made: node groups per point (1: whole groups
+// of 64 points, then tails), and whether the tails of several items share waves.
+struct UnitPlan {
+  int groups = 1;
+  bool pack = false;
+  bool operator==(const UnitPlan& o) const { return groups == o.groups && pack == o.pack; }
+};
+
+// The units of a small plan whose launches (one per depth bucket, on up to
+// 1 + kSideStreams streams) take the least estimated time: [0] plain calls, [1] calls with
+// the resolution derivative, the same unless others are 1 % faster.  Units of 400 points,
+// 10 layers, us a call at G = 1 / 2 / 3 / 6 / 9 / 17: 112 units 141 / 80 / 62 / 42 / 38 / 51; 672: 146 / 120 / 92 / 94 / 104 / 153; 1344: 212 / 170 / 156 / 166 / 176 /
+// 278; 2688: 309 / 268 / 283 / 298 / 328 / 537; 4480: 430 / 445 / 446 / 479 / 535 / 878.
+// G = 2048 / units, the rule before, took 53, 92, 211, 309 and 429 us there.  Many short
+// items gain from the lanes that groups fill: 2355 of 40 points, 10 layers FP64 with
+// resolution 315 us whole, 221 split.
+// Tails in waves of their own displace whole units: where the two do not fit the rounds
+// that the whole units take, the last of these end as much later as a tail takes (438
+// items of 400 points, 36 layers FP32, 2.57 + 0.43 units per SIMD: 966 us, 887 packed;
+// 250 items, 1.46 + 0.24: 613, 647).  Launches of other depths cover it, over many rounds
+// it does not show (3584 items of 130 to 168 points: 0.93-1.02 of the packed time at nearly
+// every depth), and packed units that spill or have a SIMD's other wave to themselves
+// give it back, so packing is tried for FP32 at one wave per SIMD (32-40 layers) alone.
+// Launches of several depths overlap, but not fully: a stream's share of them one after
+// the other plus 0.7 of the time that all would take on a full device.  kReduceUs: the
+// reduction adds an item's records one by one (in plans of one depth it is hidden in
+// the 9 us).
+// Over 420 plans of one depth (24 to 900 points, 0.3 to 6 units per SIMD, both precisions)
+// the choice is 1.4 % over the best of the eight in the mean, plain, and 1.1 % with
+// resolution; 5 % or more in one of ten, 28 % at worst.  Over 88 ragged ones (10 to 600
+// items of 100 to 1000 points) 1.6 and 2.0 %, 21 % at worst: 400 of 2 to 40 layers FP64
+// 1816 us whole, 1293 / 1306 / 1431 / 1610 in 2 / 3 / 4 / 9 groups.
 // More groups write more records.  A plan that the fixed scratch of
 // nr_loglik_grad_noalloc held with that rule's records is not pushed over it.
 constexpr int kSmallPlanWaves = 6;  // units per SIMD: from here on the plan is not split
-int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
+constexpr double kReduceUs = 0.08;
+std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simds) {
   const int G_fit = (int)std::max<int64_t>(1, std::min<int64_t>(kSmearNodes, 2 * simds / units));
-  // waves per bucket of the shallow items, and the plan's workspace
-  int64_t waves[kNumBuckets];
+  // per bucket of the shallow items: units; at G = 1 apart from those, the smeared tails
+  // of 32 points or fewer, the nodes they run in node groups, and their points per depth
+  struct Count {
+    int64_t waves = 0, tails = 0;
+    double tail_nodes = 0.0;
+    std::map<int64_t, int64_t> tail_points;
+  };
+  Count of[kNumBuckets];
+  int64_t most_records = 0;  // of an item
   auto count = [&](int G) {
     size_t doubles = consts_doubles(p);
-    std::fill(waves, waves + kNumBuckets, 0);
+    most_records = 0;
+    for (Count& c : of) c = Count();
     for (int b = 0; b < p->n_items; ++b) {
       const int s = p->dataset_of_item[b];
       const int64_t rows = p->row_off[b + 1] - p->row_off[b];
       const int bk = bucket_of((int)rows - 2);
       const bool deep = bk == kDeepBucket;
+      const int64_t nq = p->q_off[s + 1] - p->q_off[s];
       const int64_t npts = deep ? 1 : p->dqq[s] > 0.0 ? kWuPoints / G : kWuPoints;
-      const int64_t n = (p->q_off[s + 1] - p->q_off[s] + npts - 1) / npts;
+      const int64_t n = (nq + npts - 1) / npts;
       doubles += (size_t)n * (4 + 4 * (size_t)rows);
       if (deep) continue;
-      // (FP32: a short tail beside whole units runs its share of the nodes: 710
-      // items of 262 points, 26 layers 839 us whole, 1041 in two groups)
-      const int64_t tail = (p->q_off[s + 1] - p->q_off[s]) % kWuPoints;
-      const bool part = p->precision == NR_F32 && G == 1 && tail > 0 && tail <= kWuPoints / 4;
-      waves[bk] += part ? n - 1 : n;
+      most_records = std::max(most_records, n);
+      Count& c = of[bk];
+      const int tail = (int)(nq % kWuPoints);
+      const bool part = G == 1 && p->dqq[s] > 0.0 && tail > 0 && tail <= kWuPoints / 2;
+      c.waves += part ? n - 1 : n;
+      if (part) {
+        const int groups = std::min(kWuPoints / tail, (int)kSmearNodes);
+        ++c.tails;
+        c.tail_nodes += (kSmearNodes + groups - 1) / groups;
+        c.tail_points[rows] += tail;
+      }
     }
     return sizeof(double) * doubles;
   };
   const size_t limit = std::max<size_t>(count(G_fit), NR_NOALLOC_SCRATCH_BYTES);
-  double best = 0.0, whole = 1.0;
-  int best_G = 1;
-  for (int G : {1, 2, 3, 4, 5, 6, 9, 17}) {
-    if (count(G) > limit) continue;
-    const int nodes = (kSmearNodes + G - 1) / G;
+  // us, of the counts
+  auto estimate = [&](UnitPlan u, bool res) {
+    const int nodes = (kSmearNodes + u.groups - 1) / u.groups;
     int launches = 0;
+    for (const Count& c : of) launches += c.waves + c.tails > 0;
     double sum = 0.0, work = 0.0;  // launch by launch, and as one full device
     for (int k = 0; k < kNumBuckets; ++k) {
-      if (waves[k] == 0) continue;
-      ++launches;
-      const double t = launch_estimate(p->precision, kBucketLmax[k], waves[k], nodes, simds);
-      // in favour of whole nodes, whose kernels are the faster ones in FP64: 8 %, and
-      // 10 % at one wave per SIMD (2877 units of 24 layers 844 us whole, 887 in two
-      // groups); in FP32, 1500 units of 12 layers, 145 whole, 128 in two groups
-      if (G == 1 && p->precision == NR_F64)
-        whole = std::min(whole, grad_waves_per_simd(NR_F64, kBucketLmax[k]) == 1 ? 0.9 : 0.92);
-      const double one = launch_estimate(p->precision, kBucketLmax[k], 5 * simds, nodes, simds);
-      sum += t;
-      work += one / 5.2 * ((double)waves[k] / (double)simds);
+      const Count& n = of[k];
+      if (n.waves + n.tails == 0) continue;
+      const int lmax = kBucketLmax[k];
+      const LaunchCost c = launch_cost(p->precision, lmax, res, u.groups > 1);
+      const LaunchCost ct = launch_cost(p->precision, lmax, res, true);
+      const double wave = c.us * (lmax + 1) * (nodes + c.e);
+      const double each =
+          n.tails > 0 ? ct.us * (lmax + 1) * (n.tail_nodes / (double)n.tails + ct.e) : 0.0;
+      const double w = (double)n.waves / (double)simds, wt = (double)n.tails / (double)simds;
+      work += wave * c.slope * w + each * ct.slope * wt;
+      if (u.pack) {
+        int64_t packed = 0;
+        for (const auto& d : n.tail_points) packed += (d.second + kWuPoints - 9) / (kWuPoints - 8);
+        sum += 1.01 * wave * c.step(w + (double)packed / (double)simds);
+        continue;
+      }
+      if (n.waves > 0) sum += wave * c.step(w);
+      if (n.tails == 0) continue;
+      if (launches > 1 || n.waves == 0)
+        sum += each * ct.step(wt);
+      else if (w + wt > 0.97 * std::ceil(w))
+        sum += (p->precision == NR_F32 || grad_waves_per_simd(NR_F64, lmax) == 1 ? 1.0 : 1.6) * each;
     }
-    const double t = std::max(sum / std::min(std::max(launches, 1), 1 + kSideStreams), work);
-    if (best == 0.0 || t < best * (best_G == 1 ? whole : 0.98)) {
-      best = t;
-      best_G = G;
+    if (launches <= 1) return std::max(sum, work);
+    return std::max(sum / std::min(launches, 1 + kSideStreams) + 0.7 * work, work) +
+           kReduceUs * (double)most_records;
+  };
+  struct Candidate {
+    UnitPlan units;
+    double us[2];
+  };
+  std::vector<Candidate> list;
+  auto add = [&](UnitPlan u) { list.push_back({u, {estimate(u, false), estimate(u, true)}}); };
+  for (int G : {1, 2, 3, 4, 5, 6, 9, 17}) {
+    if (count(G) > limit) continue;
+    add({G, false});
+    if (G == 1 && p->precision == NR_F32 && p->opts.pack_tails) {
+      int launches = 0, pack = 0;
+      for (int k = 0; k < kNumBuckets; ++k) {
+        launches += of[k].waves + of[k].tails > 0;
+        pack += of[k].tails > 0 && of[k].waves >= simds &&
+                grad_waves_per_simd(NR_F32, kBucketLmax[k]) == 1;
+      }
+      if (launches == 1 && pack == 1) add({1, true});
     }
   }
-  return best_G;
+  std::array<UnitPlan, 2> out;
+  size_t best = 0;
+  for (int res : {0, 1}) {
+    for (size_t k = 0; k < list.size(); ++k)
+      if (list[k].us[res] < 0.99 * list[best].us[res]) best = k;
+    if (!list.empty()) out[res] = list[best].units;
+  }
+  return out;
 }
 
 // The streams of a schedule's launches.  A launch that does not fill the device,
@@ -545,7 +644,7 @@ int pick_node_groups(const nr_plan* p, int64_t units, int64_t simds) {
 //    then in a row stay in a row: two items of 20 and 2 layers 46.6 us in a row, 48-57
 //    on two streams; two of 28 and 6 60.5 / 55.3.
 constexpr double kForkCallUs = 55.0, kLaunchUs = 5.0;
-void assign_streams(GradSchedule& S, bool side, int precision, int64_t simds) {
+void assign_streams(GradSchedule& S, bool side, int64_t simds) {
   std::vector<Launch>& list = S.launches;
   S.n_side = 0;
   if (!side || list.size() < 2) return;
@@ -553,8 +652,7 @@ void assign_streams(GradSchedule& S, bool side, int precision, int64_t simds) {
   double us = 0.0;
   for (const Launch& L : list) {
     total += L.n_wu;
-    // (us per unit of the estimates, from the calls above)
-    us += (precision == NR_F32 ? 0.30 : 0.45) * L.est + kLaunchUs;
+    us += L.est + kLaunchUs;
   }
   if (us <= kForkCallUs) return;
   if (total > 48 * simds) {
@@ -1067,9 +1165,9 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
     int64_t rec0;  // record of its first point
   };
   // gradient: one list per bucket, then three deep lists (kDeepBucket + c), by
-  // the levels per lane an item needs at 64 lanes (c = 0: up to 8, 1: up to 16, 2: more), which set the waves per
-  // data point of the scan kernel (1, 2, 4), so that shallower deep items do
-  // not run with the idle lanes of the deepest one
+  // the levels per lane an item needs at 64 lanes (c = 0: up to 8, 1: up to 16,
+  // 2: more), which set the waves per data point of the scan kernel (1, 2, 4), so
+  // that shallower deep items do not run with the idle lanes of the deepest one
   constexpr int kDeepClasses = 3;
   std::vector<Wu> fwd_units;
   int scan_ch[kDeepClasses] = {0, 0, 0};
@@ -1090,7 +1188,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       simds = 4 * (int64_t)cus;
   }
   simds = std::max<int64_t>(simds, 1);
-  int small_G = 1, small_G_fwd = 1, res_G = 1;
+  UnitPlan small, small_res;  // of the gradient calls
+  int small_G_fwd = 1;
   if (p->opts.split_tails & NR_SPLIT_SMALL) {
     int64_t units = 0, units_fwd = 0, levels_fwd = 0;
     for (int b = 0; b < nI; ++b) {
@@ -1101,13 +1200,15 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       levels_fwd += u * (N + 1);
       if (bucket_of(N) != kDeepBucket) units += u;
     }
-    if (units > 0 && units < kSmallPlanWaves * simds)
-      small_G = pick_node_groups(p, units, simds);
-    // The resolution form's split kernels spend more registers on the derivative and
-    // lose from two units per SIMD on (us a call, split / whole: 1000 items of 84 points, 10
-    // layers FP64 182.9 / 171.7, 2000 of 96, 14 layers 632 / 553, 16 layers FP32 447 / 353):
-    // those calls then have a schedule of their own.
-    res_G = units < 2 * simds ? small_G : 1;
+    // The resolution form's split kernels spend more registers on the derivative: a
+    // choice of their own, and a schedule where it is another (us a call, split like
+    // the plain gradient / whole: 2000 items of 96 points, 14 layers FP64 632 / 553, 16
+    // layers FP32 447 / 353, but 2355 of 40 points, 10 layers FP64 221 / 315).
+    if (units > 0 && units < kSmallPlanWaves * simds) {
+      const std::array<UnitPlan, 2> pick = pick_units(p, units, simds);
+      small = pick[0];
+      small_res = pick[1];
+    }
     // Value units, by how many each SIMD would get unsplit.  Measured on MI355X
     // (10 layers x 400 points, us a call at G = 1 / 2 / 6 / 9): 224 units 72 /
     // 47 / 32 / 29; 448: 74 / 48 / 40 / 41; 1344: 114 / 87 / 80 / 83; 1792:
@@ -1130,7 +1231,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
                                                              : 1;
   }
   // a tiling given by the caller: every point group split over node_groups
-  if (p->opts.node_groups >= 2) small_G = res_G = p->opts.node_groups;
+  if (p->opts.node_groups >= 2) small = small_res = UnitPlan{p->opts.node_groups, false};
   // Where every lane runs one node, the two node forms do not pay for their
   // costlier constants and the scalar record loads that a wave waits for at its
   // first node: the one-form kernels.  us a call, two forms / one: 10 smeared items
@@ -1149,7 +1250,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       scan_one_node &= !smeared;
       scan_points += p->q_off[s + 1] - p->q_off[s];
     } else {
-      one_node &= !smeared || small_G == kSmearNodes;
+      one_node &= !smeared || small.groups == kSmearNodes;
     }
   }
   scan_one_node &= scan_points <= 2 * simds;
@@ -1269,8 +1370,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
                      (res || L.form != kFormSelect) &&
                      lane_counter_pays(p->precision, kBucketLmax[L.bucket], res, L.n_wu, simds);
       L.est = L.bucket == kDeepBucket
-                  ? 1.5 * 8 * nodes * L.n_wu * std::max(1, L.scan_ch / 8) / (double)simds
-                  : launch_estimate(p->precision, kBucketLmax[L.bucket], L.n_wu, nodes, simds);
+                  ? 0.68 * 8 * nodes * L.n_wu * std::max(1, L.scan_ch / 8) / (double)simds
+                  : launch_estimate(p->precision, kBucketLmax[L.bucket], split, L.n_wu, nodes, simds);
       e = upload(&L.item, it);
       keep(L.item);
       if (e == hipSuccess) { e = upload(&L.p0, p0); keep(L.p0); }
@@ -1298,9 +1399,11 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
                      (split || (int64_t)all[0].size() <= 2 * simds || steps >= 1300 * (int64_t)nI);
     make_full(kOpLoglik, all, p->launches_fwd, split);
   }
-  // the gradient's schedule with every smeared point group split over small_G
-  // node groups (1: whole groups of 64 points and tails)
-  auto build_grad = [&](int small_G, GradSchedule& S) {
+  // the gradient's schedule with every smeared point group split over the plan's node
+  // groups (1: whole groups of 64 points and tails)
+  auto build_grad = [&](UnitPlan unit_plan, GradSchedule& S) {
+    const int small_G = unit_plan.groups;
+    const int own_tails = unit_plan.pack ? 0 : p->opts.split_tails;
     std::vector<std::vector<Wu>> grad_units(kNumBuckets + kDeepClasses);
     std::vector<std::vector<Wu>> split_units(kNumBuckets);
     std::map<std::pair<int, int>, std::vector<Tail>> tails;  // (depth, nodes)
@@ -1322,7 +1425,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         const int cls = ch64 <= 8 ? 0 : ch64 <= 16 ? 1 : 2;
         scan_ch[cls] = std::max(scan_ch[cls], ch64);
         for (int64_t k = 0; k < nq; ++k) {
-          grad_units[kDeepBucket + cls].push_back({b, (int32_t)k, rec_gr, (uint32_t)(K * (N + 1) * 64)});
+          grad_units[kDeepBucket + cls].push_back(
+              {b, (int32_t)k, rec_gr, (uint32_t)(K * (N + 1) * 64)});
           gr_offs.push_back(rec_gr);
           rec_gr += rsz;
         }
@@ -1367,7 +1471,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         const int G = std::min(kWuPoints / ntail, K);
         if ((p->opts.split_tails & NR_TAILS_LONE) && (ntail >= 48 || (K > 1 && G == 1))) {
           grad_units[bk].push_back({b, nfull * kWuPoints, rec_gr, (uint32_t)(ntail * K * (N + 1))});
-        } else if ((p->opts.split_tails & NR_TAILS_SPLIT) && G >= 2) {
+        } else if ((own_tails & NR_TAILS_SPLIT) && G >= 2) {
           Wu u{b, nfull * kWuPoints, rec_gr, (uint32_t)(ntail * K * (N + 1))};
           u.split = ntail | (G << 16);
           split_units[bk].push_back(u);
@@ -1447,7 +1551,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         L.form = p->bucket_form[bk] == kFormSelect ? kFormRecompute : p->bucket_form[bk];
         L.tail = true;
         L.n_wu = (int)b_item[bk].size();
-        L.est = launch_estimate(p->precision, kBucketLmax[bk], L.n_wu, b_nodes[bk], simds);
+        L.est = launch_estimate(p->precision, kBucketLmax[bk], true, L.n_wu, b_nodes[bk], simds);
         e = upload(&L.item, b_item[bk]);
         keep(L.item);
         if (e == hipSuccess) { e = upload(&L.lane_item, b_litem[bk]); keep(L.lane_item); }
@@ -1464,11 +1568,11 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       p->grad_scaled |= L.form == kFormSelect;
       p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
     }
-    assign_streams(S, p->opts.side_stream != 0, p->precision, simds);
+    assign_streams(S, p->opts.side_stream != 0, simds);
   };
-  build_grad(small_G, p->grad);
-  p->res_own = res_G != small_G;
-  if (p->res_own) build_grad(res_G, p->grad_res);
+  build_grad(small, p->grad);
+  p->res_own = !(small_res == small);
+  if (p->res_own) build_grad(small_res, p->grad_res);
   if (std::max(p->grad.n_side, p->grad_res.n_side) > 0 && e == hipSuccess) {
     e = side_pool_acquire(p->device);
     p->pooled = e == hipSuccess;

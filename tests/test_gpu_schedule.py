@@ -70,13 +70,15 @@ def test_value_form_of_items_of_little_work(nr, orc, L, nq, items, forms):
         check_logL(ll[b], llo, logL_bound(Ro, Robs, e))
 
 
-def test_resolution_calls_of_two_units_per_simd_are_not_split(nr):
+def test_resolution_calls_have_units_of_their_own(nr):
+    """Split in node groups, the plain call is the faster, the one with the resolution
+    derivative the slower (14 layers FP64: its split kernel spills twice as much)."""
     import torch
-    batch = _batch(6, 84, 1024)
+    batch = _batch(14, 100, 1536)
     p = nr.Problem.from_batch(batch)
     assert {x["mode"] for x in p.plan.launches()} == {nr._n.NR_MODE_SPLIT}
     whole = nr.Problem.from_batch(batch, options={"split_tails": 3})
-    assert {x["mode"] for x in whole.plan.launches()} == {nr._n.NR_MODE_FULL, nr._n.NR_MODE_SPLIT}
+    assert {x["mode"] for x in whole.plan.launches()} == {nr._n.NR_MODE_FULL}
     for x, y in zip(p.loglik_grad_res(), whole.loglik_grad_res()):
         assert torch.equal(x, y)
     # the plain call's records and the other schedule's share the workspace
