@@ -506,7 +506,8 @@ struct UnitPlan {
 // 250 items, 1.46 + 0.24: 613, 647).  Launches of other depths cover it, over many rounds
 // it does not show (3584 items of 130 to 168 points: 0.93-1.02 of the packed time at nearly
 // every depth), and packed units that spill or have a SIMD's other wave to themselves
-// give it back, so packing is tried for FP32 at one wave per SIMD (32-40 layers) alone.
+// give it back, so packing is tried at one wave per SIMD in one-form kernels alone (FP32
+// 32-40 layers, FP64 40: 300 items of 400 points 1306 us, 1170 packed).
 // Launches of several depths overlap, but not fully: a stream's share of them one after
 // the other plus 0.7 of the time that all would take on a full device.  kReduceUs: the
 // reduction adds an item's records one by one (in plans of one depth it is hidden in
@@ -587,7 +588,7 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
       if (n.tails == 0) continue;
       if (launches > 1 || n.waves == 0)
         sum += each * ct.step(wt);
-      else if (w + wt > 0.97 * std::ceil(w))
+      else if (w + wt > 0.985 * std::ceil(w))
         sum += (p->precision == NR_F32 || grad_waves_per_simd(NR_F64, lmax) == 1 ? 1.0 : 1.6) * each;
     }
     if (launches <= 1) return std::max(sum, work);
@@ -603,12 +604,12 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
   for (int G : {1, 2, 3, 4, 5, 6, 9, 17}) {
     if (count(G) > limit) continue;
     add({G, false});
-    if (G == 1 && p->precision == NR_F32 && p->opts.pack_tails) {
+    if (G == 1 && p->opts.pack_tails) {
       int launches = 0, pack = 0;
       for (int k = 0; k < kNumBuckets; ++k) {
         launches += of[k].waves + of[k].tails > 0;
-        pack += of[k].tails > 0 && of[k].waves >= simds &&
-                grad_waves_per_simd(NR_F32, kBucketLmax[k]) == 1;
+        pack += of[k].tails > 0 && of[k].waves >= simds && p->bucket_form[k] != kFormSelect &&
+                grad_waves_per_simd(p->precision, kBucketLmax[k]) == 1;
       }
       if (launches == 1 && pack == 1) add({1, true});
     }
@@ -634,17 +635,19 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
 //    kernels of different register budgets mix on a SIMD (16384 items in FP32 22.5 ->
 //    23.4 ms, in FP64 36.9 both): it keeps two streams, alternating from bucket to
 //    bucket, with the small launches beside them.
-//  * Split and packed launches of more than three waves per SIMD fill the device
-//    alone and stay on the caller's stream (beside / after, us a call: 4096 draws of
-//    10 layers x 400 points, 4096 split units 2254 / 2225, x 80 points 552 / 518, 28
-//    layers x 90 points 2066 / 1993; but 2300 draws, 2300 split units 1279 / 1309, 28
-//    layers x 90 points, 1100 split units 686 / 979).
+//  * Where the whole units of a plan of one depth leave no room in their last round, a
+//    split or packed launch of more than three waves per SIMD, which fills the device
+//    alone, comes after them (beside / after, us a call: 4096 draws of 10 layers x 400
+//    points, 24 and 4 units per SIMD, 2254 / 2225, x 80 points 552 / 518, 28 layers x 90
+//    points 2066 / 1993; but 4200 draws of 10 layers FP64 x 80 points 580 / 637, x 90 643
+//    / 724, x 209 1312 / 1358, x 400 2398 / 2409, 6500 of 20 layers FP32 x 90 1184 / 1297, and
+//    beside is the faster one for 117 of 120 such plans of 4 to 36 layers).
 //  * A call that forks takes some 55 us however short its kernels are (events and
 //    waits, on the host and across hardware queues), so launches that are done by
 //    then in a row stay in a row: two items of 20 and 2 layers 46.6 us in a row, 48-57
 //    on two streams; two of 28 and 6 60.5 / 55.3.
 constexpr double kForkCallUs = 55.0, kLaunchUs = 5.0;
-void assign_streams(GradSchedule& S, bool side, int64_t simds) {
+void assign_streams(GradSchedule& S, bool side, int precision, int64_t simds) {
   std::vector<Launch>& list = S.launches;
   S.n_side = 0;
   if (!side || list.size() < 2) return;
@@ -666,10 +669,22 @@ void assign_streams(GradSchedule& S, bool side, int64_t simds) {
   }
   std::stable_sort(list.begin(), list.end(),
                    [](const Launch& x, const Launch& y) { return x.est > y.est; });
+  // what the whole units of the one depth leave idle of a wave per SIMD
+  int whole = 0;
+  double idle = 1.0;
+  for (const Launch& L : list) {
+    if (L.tail || L.split) continue;
+    const double per = L.bucket == kDeepBucket
+                           ? 1.0
+                           : grad_waves_per_simd(precision, kBucketLmax[L.bucket]);
+    const double rounds = (double)L.n_wu / (per * (double)simds);
+    ++whole;
+    idle = per * (std::ceil(rounds) - rounds);
+  }
   double load[1 + kSideStreams] = {};
   for (Launch& L : list) {
-    const bool large = (L.tail || L.split) && L.n_wu > 3 * simds;
-    L.side = large ? 0 : (int)(std::min_element(load, load + 1 + kSideStreams) - load);
+    const bool after = (L.tail || L.split) && L.n_wu > 3 * simds && whole == 1 && idle < 0.05;
+    L.side = after ? 0 : (int)(std::min_element(load, load + 1 + kSideStreams) - load);
     load[L.side] += L.est;
     S.n_side = std::max(S.n_side, L.side);
   }
@@ -1568,7 +1583,7 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       p->grad_scaled |= L.form == kFormSelect;
       p->scan_select |= L.form == kFormSelect && L.bucket == kDeepBucket;
     }
-    assign_streams(S, p->opts.side_stream != 0, simds);
+    assign_streams(S, p->opts.side_stream != 0, p->precision, simds);
   };
   build_grad(small, p->grad);
   p->res_own = !(small_res == small);

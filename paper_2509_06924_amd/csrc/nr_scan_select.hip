@@ -13,9 +13,10 @@
 //    for the whole workgroup (one data point, one item), and the phase
 //    cotangent from the state leaving the level.
 //  * Records in the order that the lanes read them (LaneRecords).
-// Two waves per SIMD as there; what bounds it is the FP64 VALU (active 0.81 of
-// the time in both) with the waits of the scans' shuffles and barriers: 4175
-// VALU instructions per node and wave at 1000 slabs before, 3548 now.  Measured
+// Two waves per SIMD as there; what bounds it is the FP64 VALU (active 0.42 of each
+// wave's cycles in both) with the waits of the scans' shuffles and barriers (0.19
+// before, 0.23 now): 4175 VALU instructions per node and wave at 1000 slabs before,
+// 3547 now.  Measured
 // on MI355X, us a call (5 % dQ/Q): 64 x 1000 slabs x 200 points 4290 -> 3640;
 // x 150 points: 16 x 50 slabs 163 -> 129, 16 x 100 187 -> 158, 16 x 200 290 ->
 // 239, 16 x 450 503 -> 445, 8 x 800 492 -> 435, 4 x 1500 526 -> 445.
@@ -38,7 +39,7 @@ struct ScanRec {
 // (Nr, Ni), (pd, lc), so that the lanes' loads of one level are contiguous.
 // With the rows in item order each lane's 16 bytes came from a cache line of
 // their own and the waves waited on the L1 (64 lines a load): the 1000-slab
-// batch 4.28 ms, with 17 % fewer VALU instructions than before them.  Up to two
+// batch 4.28 ms, as with the prefix scan.  Up to two
 // rows past a lane's last are read ahead of their use; they lie in the item's
 // part of the workspace and are not used.
 // (the workspace is only known to be aligned for doubles)

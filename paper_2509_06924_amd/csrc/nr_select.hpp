@@ -12,13 +12,14 @@
 //   general  any stack at any q.
 //
 // Both give the function to rounding; the choice follows from the values of a
-// node alone.  What bounds these kernels is the FP64 VALU: at two waves per
-// SIMD it is active 0.91-0.95 of a launch, and v_rsq_f64 and v_rcp_f64 hold it
-// for four instructions (16 cycles measured on MI355X at one to eight waves
-// per SIMD, against 4 for an FMA).  So the forms differ in instructions per
-// level: at 10 layers 235 VALU instructions per level in the general form and
-// 205 in the above form, 5.4 and 3.4 of them transcendental, against 249 and
-// 5.4 in k_loglik_grad.
+// node alone.  What bounds these kernels is the FP64 VALU: it is active for 0.47
+// of each wave's cycles at two waves per SIMD (10 layers), and v_rsq_f64 and
+// v_rcp_f64 hold it for four instructions (16 cycles measured on MI355X at one to
+// eight waves per SIMD, against 4 for an FMA).  So the forms differ in instructions
+// per level: at 10 layers, epilogue and all, 244 VALU instructions per level and
+// node where every node is general and 214 where every node is above, 5.4 and 3.4
+// of them transcendental, against 254 and 5.4 in k_loglik_grad (counters of 2048
+// items x 448 points at q below 0.009 and above 0.25, 1580 and 1430 us).
 //
 // Measured on MI355X against k_loglik_grad (2048 draws x 448 points, 5 %
 // dQ/Q, about 0.6 of the nodes above; one box, us):
@@ -29,8 +30,7 @@
 // and more from 24 layers on) crowd the instruction cache that two compute
 // units share, so units in flight together should run the same form: ordered
 // by their place in the data set instead of item by item, 16-20 layers gained
-// 4-5 % (28 layers item by item: 200 cache misses a wave against 13, a seventh
-// of its time).  40 layers run 10 % slower (464 B of spill beside 200 KB of
+// 4-5 %.  40 layers run 10 % slower (464 B of spill beside 200 KB of
 // code).  Packed tail units spilled up to 1 KB here and stay with
 // k_loglik_grad, and so do the resolution form and FP32 (whose exponentials
 // are hardware functions).

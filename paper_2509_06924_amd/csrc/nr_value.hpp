@@ -38,9 +38,10 @@ __device__ __forceinline__ double node_reflectivity(const MathTables& T, const L
 }
 
 // The same in FP64, in the node form that the caller tested (nr_select.hpp).
-// Bound by the FP64 VALU like the gradient kernels: 141 VALU instructions per
-// level in node_reflectivity, 3 of them transcendental; here 131 in the
-// general form and 104 and 2 in the above form.  4096 draws x 10 layers x 400
+// Bound by the FP64 VALU like the gradient kernels: at 10 layers 129 VALU
+// instructions per level and node, 3.1 of them transcendental, where every node is
+// general, 105 and 2.1 where every node is above (778 and 644 us for 2048 items x
+// 448 points under the counters).  4096 draws x 10 layers x 400
 // points: 1.40 ms with one kernel per depth bucket and whole waves for partial
 // groups, 1.15 with these units and node forms, 1.09 with levels in pairs (no
 // register moves from one level to the next); four waves per SIMD (100 VGPRs)

@@ -91,13 +91,14 @@ def _streams(p):
     return [x["stream"] for x in p.plan.launches()]
 
 
-def test_split_launch_that_fills_the_device_stays_on_the_callers_stream(nr):
+def test_split_launch_comes_after_whole_units_that_fill_their_rounds(nr):
     # 400 points: six whole units per item and a tail of 16, in a split launch
-    p = nr.Problem.from_batch(_batch(6, 400, 3072))
+    p = nr.Problem.from_batch(_batch(6, 400, 4096))
     assert [(x["mode"], x["units"], x["stream"]) for x in p.plan.launches()] == [
-        (nr._n.NR_MODE_FULL, 6 * 3072, 0), (nr._n.NR_MODE_SPLIT, 3072, 1)]
-    p = nr.Problem.from_batch(_batch(6, 400, 3073))
-    assert _streams(p) == [0, 0]
+        (nr._n.NR_MODE_FULL, 6 * 4096, 0), (nr._n.NR_MODE_SPLIT, 4096, 0)]
+    # three waves per SIMD, and room in the last round
+    assert _streams(nr.Problem.from_batch(_batch(6, 400, 3072))) == [0, 1]
+    assert _streams(nr.Problem.from_batch(_batch(6, 400, 4200))) == [0, 1]
 
 
 def test_launches_shorter_than_a_fork_stay_in_a_row(nr):
