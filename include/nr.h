@@ -192,8 +192,11 @@ nr_status nr_plan_create(const nr_batch_desc* desc, nr_plan** plan_out);
  *                       of a smeared item of at most NR_MAX_LAYERS layers is
  *                       split the same way, over the G of 1, 2, 3, 4, 5, 6, 9 or
  *                       17 node groups that finishes first by a measured
- *                       model, so that a single fit spreads over many waves;
- *                       the value calls split below three units per SIMD.
+ *                       model, so that a single fit spreads over many waves
+ *                       (calls with the resolution derivative by a model of
+ *                       their own; deep one-form kernels may pack the tails
+ *                       instead); the value calls split below three units per
+ *                       SIMD.
  *     Default: all three bits.
  *   side_stream: 1 (default) spreads the gradient's launches (one per
  *     layer-count bucket and kind of unit) over the caller's stream and up to

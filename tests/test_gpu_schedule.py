@@ -105,3 +105,30 @@ def test_launches_shorter_than_a_fork_stay_in_a_row(nr):
     assert _streams(nr.Problem.from_batch(_batch([20, 2], 200, 2))) == [0, 0]
     assert max(_streams(nr.Problem.from_batch(_batch([36, 28], 200, 2)))) == 1
     assert max(_streams(nr.Problem.from_batch(_batch([40, 30, 20, 10], 300, 4)))) == 3
+
+
+@pytest.mark.parametrize("precision,L", [("f64", 40), ("f32", 33), ("f32", 40)])
+def test_tails_that_would_displace_whole_units_share_waves(nr, precision, L):
+    """300 items of 400 points: 1800 whole units and 300 tails are more than two rounds of
+    1024 SIMDs, with four tails of 16 points in a wave they are not."""
+    p32 = precision == "f32"
+    batch = _batch(L, 400, 300)
+    make = lambda o=None: nr.Problem.from_batch(  # noqa: E731
+        batch, precision=nr.NR_F32 if p32 else nr.NR_F64, options=o)
+    p, own = make(), make({"split_tails": 3})
+    M = nr._n
+    assert {(x["mode"], x["units"]) for x in p.plan.launches()} == {
+        (M.NR_MODE_FULL, 1800), (M.NR_MODE_PACKED, 75)}
+    assert {(x["mode"], x["units"]) for x in own.plan.launches()} == {
+        (M.NR_MODE_FULL, 1800), (M.NR_MODE_SPLIT, 300)}
+    got, want = ([t.cpu().numpy() for t in x.loglik_grad()] for x in (p, own))
+    # sums in another order (tests/test_gpu_autotune.py); FP32 nodes: the variant's bound
+    assert np.allclose(got[0], want[0], rtol=1e-4 if p32 else 1e-12, atol=0)
+    units = np.array([1.0, 1e-6, 1e-6, 1.0])
+    scale = np.max(np.abs(want[1] * units))
+    assert np.max(np.abs((got[1] - want[1]) * units)) <= (1e-4 if p32 else 1e-10) * scale
+    # fewer whole units than SIMDs, or room for the tails: waves of their own, or groups
+    for items in (100, 250):
+        modes = {x["mode"] for x in nr.Problem.from_batch(
+            _batch(L, 400, items), precision=p.plan.precision).plan.launches()}
+        assert M.NR_MODE_PACKED not in modes
