@@ -160,7 +160,7 @@ size_t xcd_order(size_t b, size_t n, size_t run) {
 // The order of units by `key`, ascending, equal keys as they are: counting passes
 // over the keys' bytes, without those that all keys share.  Comparing the units of
 // 4096 draws (57 000 in two lists of seven costs and places) took 0.4 ms of a plan's
-// 1.65, those of 16384 ragged items 6 of 16 ms.
+// 1.65, those of 16384 ragged items 10 of 16 ms.
 std::vector<uint32_t> order_by(const std::vector<uint64_t>& key) {
   const size_t n = key.size();
   std::vector<uint32_t> idx(n), next(n);
@@ -183,13 +183,38 @@ std::vector<uint32_t> order_by(const std::vector<uint64_t>& key) {
   return idx;
 }
 
+// Device copies of host arrays, in one allocation and one copy: a plan has dozens of
+// small ones, at some 15 us each (64 items of 400 points 626 us a plan one by one, 295
+// so; 400 ragged items 1535 / 609).
 template <class T>
-hipError_t upload(T** dst, const std::vector<T>& src) {
+struct Part {
+  T** dst;  // null for an empty array
+  const std::vector<T>& src;
+  size_t bytes() const { return (src.size() * sizeof(T) + 255) / 256 * 256; }
+  void stage(unsigned char* host, unsigned char* device, size_t& at) const {
+    if (src.empty()) return;
+    std::memcpy(host + at, src.data(), src.size() * sizeof(T));
+    *dst = reinterpret_cast<T*>(device + at);
+    at += bytes();
+  }
+};
+template <class T>
+Part<T> part(T** dst, const std::vector<T>& src) {
   *dst = nullptr;
-  if (src.empty()) return hipSuccess;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(dst), src.size() * sizeof(T));
+  return {dst, src};
+}
+template <class... T>
+hipError_t upload(std::vector<void*>& owned, Part<T>... parts) {
+  const size_t total = (parts.bytes() + ...);
+  if (total == 0) return hipSuccess;
+  void* device = nullptr;
+  const hipError_t e = hipMalloc(&device, total);
   if (e != hipSuccess) return e;
-  return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
+  owned.push_back(device);
+  std::vector<unsigned char> host(total);
+  size_t at = 0;
+  (parts.stage(host.data(), static_cast<unsigned char*>(device), at), ...);
+  return hipMemcpy(device, host.data(), total, hipMemcpyHostToDevice);
 }
 
 // Streams beside the caller's for the gradient's launches (four in all, the
@@ -1298,19 +1323,6 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
   p->rec_ll_total = rec_ll;
 
   hipError_t e = hipSuccess;
-  auto keep = [&](void* ptr) { p->owned.push_back(ptr); };
-  e = upload(&p->d_dataset_of_item, p->dataset_of_item);
-  keep(p->d_dataset_of_item);
-  if (e == hipSuccess) { e = upload(&p->d_q_off, p->q_off); keep(p->d_q_off); }
-  if (e == hipSuccess) { e = upload(&p->d_row_off, p->row_off); keep(p->d_row_off); }
-  if (e == hipSuccess) { e = upload(&p->d_dqq, p->dqq); keep(p->d_dqq); }
-  if (e == hipSuccess) { e = upload(&p->d_out_off, p->out_off); keep(p->d_out_off); }
-  auto upload_lists = [&](RecordLists& L, const std::vector<int64_t>& first,
-                          const std::vector<int32_t>& count, const std::vector<int64_t>& offs) {
-    if (e == hipSuccess) { e = upload(&L.first, first); keep(L.first); }
-    if (e == hipSuccess) { e = upload(&L.count, count); keep(L.count); }
-    if (e == hipSuccess) { e = upload(&L.offs, offs); keep(L.offs); }
-  };
   {
     std::vector<uint8_t> kind((size_t)p->row_off.back(), 1);
     p->uniform_rows = nI > 0 ? (int)(p->row_off[1] - p->row_off[0]) : 0;
@@ -1319,15 +1331,15 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       kind[(size_t)p->row_off[b + 1] - 1] = 2;
       if (p->row_off[b + 1] - p->row_off[b] != p->uniform_rows) p->uniform_rows = 0;
     }
-    if (e == hipSuccess) { e = upload(&p->d_row_kind, kind); keep(p->d_row_kind); }
-  }
-  upload_lists(p->lists_ll, ll_first, ll_count, ll_offs);
-  if (e == hipSuccess) {
     std::vector<double> rule(p->node_t, p->node_t + kSmearNodes);
     rule.insert(rule.end(), p->node_w, p->node_w + kSmearNodes);
     append_math_tables(rule);
-    e = upload(&p->d_rule, rule);
-    keep(p->d_rule);
+    e = upload(p->owned, part(&p->d_dataset_of_item, p->dataset_of_item),
+               part(&p->d_q_off, p->q_off), part(&p->d_row_off, p->row_off),
+               part(&p->d_dqq, p->dqq), part(&p->d_out_off, p->out_off),
+               part(&p->d_row_kind, kind), part(&p->lists_ll.first, ll_first),
+               part(&p->lists_ll.count, ll_count), part(&p->lists_ll.offs, ll_offs),
+               part(&p->d_rule, rule));
   }
 
   // full-unit launches: one per non-empty bucket, deepest first, LPT order
@@ -1387,11 +1399,9 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       L.est = L.bucket == kDeepBucket
                   ? 0.68 * 8 * nodes * L.n_wu * std::max(1, L.scan_ch / 8) / (double)simds
                   : launch_estimate(p->precision, kBucketLmax[L.bucket], split, L.n_wu, nodes, simds);
-      e = upload(&L.item, it);
-      keep(L.item);
-      if (e == hipSuccess) { e = upload(&L.p0, p0); keep(L.p0); }
-      if (e == hipSuccess) { e = upload(&L.rec, rc); keep(L.rec); }
-      if (e == hipSuccess && split) { e = upload(&L.split_code, sc); keep(L.split_code); }
+      if (!split) sc.clear();
+      e = upload(p->owned, part(&L.item, it), part(&L.p0, p0), part(&L.rec, rc),
+                 part(&L.split_code, sc));
       out_list.push_back(L);
     }
   };
@@ -1498,7 +1508,9 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
       }
     }
     S.records = rec_gr;
-    upload_lists(S.lists, gr_first, gr_count, gr_offs);
+    if (e == hipSuccess)
+      e = upload(p->owned, part(&S.lists.first, gr_first), part(&S.lists.count, gr_count),
+                 part(&S.lists.offs, gr_offs));
 
     std::vector<Launch> tail_launches;  // after the full units
     // tail launches: per (depth, nodes) group, largest tails first, first fit
@@ -1567,11 +1579,8 @@ nr_status nr_plan_create_ex(const nr_batch_desc* d, const nr_plan_options* opts,
         L.tail = true;
         L.n_wu = (int)b_item[bk].size();
         L.est = launch_estimate(p->precision, kBucketLmax[bk], true, L.n_wu, b_nodes[bk], simds);
-        e = upload(&L.item, b_item[bk]);
-        keep(L.item);
-        if (e == hipSuccess) { e = upload(&L.lane_item, b_litem[bk]); keep(L.lane_item); }
-        if (e == hipSuccess) { e = upload(&L.lane_pt, b_lpt[bk]); keep(L.lane_pt); }
-        if (e == hipSuccess) { e = upload(&L.lane_rec, b_lrec[bk]); keep(L.lane_rec); }
+        e = upload(p->owned, part(&L.item, b_item[bk]), part(&L.lane_item, b_litem[bk]),
+                   part(&L.lane_pt, b_lpt[bk]), part(&L.lane_rec, b_lrec[bk]));
         tail_launches.push_back(L);
       }
     }
