@@ -548,10 +548,12 @@ constexpr int kSmallPlanWaves = 6;  // units per SIMD: from here on the plan is 
 constexpr double kReduceUs = 0.08;
 std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simds) {
   const int G_fit = (int)std::max<int64_t>(1, std::min<int64_t>(kSmearNodes, 2 * simds / units));
-  // per bucket of the shallow items: units; at G = 1 apart from those, the smeared tails
-  // of 32 points or fewer, the nodes they run in node groups, and their points per depth
+  // per bucket of the shallow items: units; apart from those, units of unsmeared items
+  // (one node each) and, at G = 1, the smeared tails of 32 points or fewer, the nodes they
+  // run in node groups, and their points per depth
   struct Count {
-    int64_t waves = 0, tails = 0;
+    int64_t waves = 0, flat = 0, tails = 0;
+    int64_t all() const { return waves + flat + tails; }
     double tail_nodes = 0.0;
     std::map<int64_t, int64_t> tail_points;
   };
@@ -573,8 +575,12 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
       if (deep) continue;
       most_records = std::max(most_records, n);
       Count& c = of[bk];
+      if (!(p->dqq[s] > 0.0)) {
+        c.flat += n;
+        continue;
+      }
       const int tail = (int)(nq % kWuPoints);
-      const bool part = G == 1 && p->dqq[s] > 0.0 && tail > 0 && tail <= kWuPoints / 2;
+      const bool part = G == 1 && tail > 0 && tail <= kWuPoints / 2;
       c.waves += part ? n - 1 : n;
       if (part) {
         const int groups = std::min(kWuPoints / tail, (int)kSmearNodes);
@@ -590,11 +596,11 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
   auto estimate = [&](UnitPlan u, bool res) {
     const int nodes = (kSmearNodes + u.groups - 1) / u.groups;
     int launches = 0;
-    for (const Count& c : of) launches += c.waves + c.tails > 0;
+    for (const Count& c : of) launches += c.all() > 0;
     double sum = 0.0, work = 0.0;  // launch by launch, and as one full device
     for (int k = 0; k < kNumBuckets; ++k) {
       const Count& n = of[k];
-      if (n.waves + n.tails == 0) continue;
+      if (n.all() == 0) continue;
       const int lmax = kBucketLmax[k];
       const LaunchCost c = launch_cost(p->precision, lmax, res, u.groups > 1);
       const LaunchCost ct = launch_cost(p->precision, lmax, res, true);
@@ -603,6 +609,11 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
           n.tails > 0 ? ct.us * (lmax + 1) * (n.tail_nodes / (double)n.tails + ct.e) : 0.0;
       const double w = (double)n.waves / (double)simds, wt = (double)n.tails / (double)simds;
       work += wave * c.slope * w + each * ct.slope * wt;
+      if (n.flat > 0) {
+        const double one = ct.us * (lmax + 1) * (1.0 + ct.e), wf = (double)n.flat / (double)simds;
+        sum += one * ct.step(wf);
+        work += one * ct.slope * wf;
+      }
       if (u.pack) {
         int64_t packed = 0;
         for (const auto& d : n.tail_points) packed += (d.second + kWuPoints - 9) / (kWuPoints - 8);
@@ -632,7 +643,7 @@ std::array<UnitPlan, 2> pick_units(const nr_plan* p, int64_t units, int64_t simd
     if (G == 1 && p->opts.pack_tails) {
       int launches = 0, pack = 0;
       for (int k = 0; k < kNumBuckets; ++k) {
-        launches += of[k].waves + of[k].tails > 0;
+        launches += of[k].all() > 0;
         pack += of[k].tails > 0 && of[k].waves >= simds && p->bucket_form[k] != kFormSelect &&
                 grad_waves_per_simd(p->precision, kBucketLmax[k]) == 1;
       }
